@@ -387,7 +387,8 @@ int bri_stencil_time(const bri_geom *geom, const void *W, int prec, const void *
                      const bri_stencil_cfg *cfg, int reps, double *us_per_launch, void *stream);
 
 /* bri_autotune -- times every candidate configuration for (geom, prec, nrhs)
- * as bri_stencil_time does and installs the fastest in a process-wide table
+ * as bri_stencil_time does, and the default, and installs the fastest in a process-wide table (none if
+ * the default is the fastest; best is then what bri_get_stencil_cfg gives)
  * used by the Brillouin stencils (bri_apply, bri_apply_dag and the overlap solvers on the
  * Brillouin kernel) for that lattice, precision and column count; the Wilson stencil keeps
  * the default configuration.  best / best_us may be NULL. */
@@ -395,7 +396,9 @@ int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, 
                  bri_stencil_cfg *best, double *best_us, void *stream);
 
 /* bri_set_stencil_cfg -- installs cfg for (geom, prec, nrhs); cfg = NULL removes
- * the entry.  bri_get_stencil_cfg -- the configuration a launch would use. */
+ * the entry.  bri_get_stencil_cfg -- the installed configuration, or the default one in the terms
+ * of bri_stencil_cfg (64-site tiles; without an entry, launches on lattices whose x-lines do not fill
+ * 64 lanes, and on fewer than 257 tiles, use tiles and wave counts that the struct cannot express). */
 int bri_set_stencil_cfg(const bri_geom *geom, int prec, int nrhs, const bri_stencil_cfg *cfg);
 int bri_get_stencil_cfg(const bri_geom *geom, int prec, int nrhs, bri_stencil_cfg *cfg);
 

@@ -724,7 +724,6 @@ struct MsSolve {
     double *partial = nullptr;
     int *alldone = nullptr;
     void *r = nullptr, *p = nullptr, *t = nullptr, *y = nullptr, *x = nullptr, *ps = nullptr;
-    int nblk_st = 0;
     // deferred shift updates: window state, the base direction at the
     // window's start and the stored residuals, per phase
     bool windowed = false;
@@ -732,9 +731,9 @@ struct MsSolve {
     void *P0 = nullptr, *R = nullptr, *P0_lo = nullptr, *R_lo = nullptr;
 
 
-    void carve(Arena &ar) {
-        nblk_st = stencil_blocks(g);
-        const int nb = nblk_st > INIT_BLOCKS ? nblk_st : INIT_BLOCKS;
+    void carve(Arena &ar) { carve(ar, stencil_max_slots(g)); }
+    void carve(Arena &ar, int nslots) {
+        const int nb = nslots > INIT_BLOCKS ? nslots : INIT_BLOCKS;
         st = (ColState *)ar.take(sizeof(ColState) * ncol);
         partial = (double *)ar.take(sizeof(double) * 2 * (size_t)nb * ncol);
         alldone = (int *)ar.take(sizeof(int));
@@ -924,6 +923,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
     struct Phase {
         int prec;
         StencilConfig cfg;
+        int nslots;  // partial sums per column its stencils leave
         StencilArgs a1, a2;
         void *r, *p, *ps;
         void *P0, *R;  // deferred updates: base direction at the window's start, stored residuals
@@ -932,6 +932,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         Phase ph;
         ph.prec = prec;
         ph.cfg = default_config(s.g, prec, s.ncol, s.kind);
+        ph.nslots = stencil_slots(s.g, ph.cfg);
         ph.a1 = StencilArgs{};
         ph.a1.g = s.g;
         ph.a1.W = W;
@@ -963,9 +964,9 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
     // one CG iteration for every column: t = X p, alpha, r update, beta, vector updates, done flags
     auto iteration = [&](const Phase &ph, bool lo, hipStream_t q) -> int {
         const int e1 = stencil_launch(ph.a1, ph.prec, false, EPI_NORMS, ph.cfg, q);
-        hipLaunchKernelGGL(ms_alpha_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, s.nblk_st);
+        hipLaunchKernelGGL(ms_alpha_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, ph.nslots);
         const int e2 = stencil_launch(ph.a2, ph.prec, true, EPI_CG_R, ph.cfg, q);
-        hipLaunchKernelGGL(ms_beta_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, s.nblk_st,
+        hipLaunchKernelGGL(ms_beta_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, ph.nslots,
                            s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
         if (s.windowed && !lo)
             hipLaunchKernelGGL((ms_pupdate_kernel<double2>), ugrid, dim3(256), 0, q, s.st, s.ws, n, s.ncol,
@@ -1050,7 +1051,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         const StencilConfig &cfg = phases[phase].cfg;
         for (uint64_t v : {(uint64_t)phase, (uint64_t)nblock, (uint64_t)cfg.tile[0], (uint64_t)cfg.tile[1],
                            (uint64_t)cfg.tile[2], (uint64_t)cfg.tile[3], (uint64_t)cfg.colz, (uint64_t)cfg.coly, (uint64_t)cfg.nsplit,
-                           (uint64_t)cfg.rpt, (uint64_t)cfg.xcd_remap, (uint64_t)cfg.variant, (uint64_t)win_at,
+                           (uint64_t)cfg.rpt, (uint64_t)cfg.xcd_remap, (uint64_t)cfg.variant, (uint64_t)cfg.lines, (uint64_t)win_at,
                            (uint64_t)first})
             k.push_back(v);
         return k;
@@ -1226,8 +1227,11 @@ static void fill_stats(const RunStats &rs, int n, ov_stats *st) {
 // Static workspace of the entry point that allocates nothing (ov_apply_noalloc): one per GPU,
 // held until the process ends, resolved once per device with hipGetSymbolAddress (the array's
 // name is only a host-side stand-in).  Every call on a GPU shares it.
-constexpr size_t SCRATCH_BYTES = (size_t)256 << 20;
-static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
+// Whether a problem fits is decided with one pair of partial sums per 64 sites; the array is larger by
+// what the launches with smaller tiles may leave (16 bytes per 64 sites and column more, and a problem
+// that fits has at most 256 MiB / (4 vectors of 192 bytes) = 350000 sites and columns).
+constexpr size_t SCRATCH_BYTES = (size_t)256 << 20, SCRATCH_SLACK = (size_t)1 << 20;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + SCRATCH_SLACK];
 constexpr int SCRATCH_MAX_DEVICES = 64;
 static std::mutex g_scratch_mu;
 static void *g_scratch_ptr[SCRATCH_MAX_DEVICES];
@@ -1267,11 +1271,11 @@ static int ov_impl(const bri_geom *geom, const void *W64, const void *Wlo, const
     size_t scratch_bytes = 0;
     if (noalloc) {
         Arena ar(nullptr);
-        m.carve(ar);
+        m.carve(ar, g.V / 64);
         if (ar.used > SCRATCH_BYTES) return BRI_ESCRATCH;
         rc = scratch_address(&work);
         if (rc != BRI_OK) return rc;
-        scratch_bytes = SCRATCH_BYTES;
+        scratch_bytes = SCRATCH_BYTES + SCRATCH_SLACK;
         work_bytes = &scratch_bytes;
     }
     {

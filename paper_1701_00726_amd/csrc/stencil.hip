@@ -86,14 +86,33 @@ int plan_tile(const Geom &g, const StencilConfig &cfg, int tile[4], int nb[4]) {
     return BRI_OK;
 }
 
+// tiles of `n` whole x-lines, the last tile of a (z, t) plane possibly with fewer
+static int line_tiles(const Geom &g, int n) { return (g.L[1] + n - 1) / n * g.L[2] * g.L[3]; }
+
+int stencil_slots(const Geom &g, const StencilConfig &cfg) {
+    return cfg.lines > 0 ? line_tiles(g, cfg.lines) : g.V / 64;
+}
+
 int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilConfig &cfg, hipStream_t st) {
     if (a.ncol < 1 || a.ncol > 65535) return BRI_EINVAL;
-    int rc = plan_tile(a.g, cfg, a.tile, a.nb);
+    int rc = BRI_OK;
+    if (cfg.lines > 0) {
+        const int n = cfg.lines;
+        a.tile[0] = a.g.L[0];
+        a.tile[1] = n;
+        a.tile[2] = a.tile[3] = 1;
+        a.nb[0] = 1;
+        a.nb[1] = (a.g.L[1] + n - 1) / n;
+        a.nb[2] = a.g.L[2];
+        a.nb[3] = a.g.L[3];
+    } else {
+        rc = plan_tile(a.g, cfg, a.tile, a.nb);
+    }
     if (rc != BRI_OK) return rc;
     a.colz = cfg.colz;
     a.coly = cfg.coly > 0 ? cfg.coly : 1;
     a.xcd_remap = cfg.xcd_remap;
-    a.nslots = a.g.V / 64;
+    a.nslots = stencil_slots(a.g, cfg);
     if (a.kind != KERN_BRI && a.kind != KERN_WIL) return BRI_EINVAL;
     const bool wil = a.kind == KERN_WIL;
     hipError_t e;
@@ -129,10 +148,10 @@ static bool xline_fits(const Geom &g) {
     return g.V / 64 >= 8192 && (g.L[0] == 16 || g.L[0] == 32 || g.L[0] == 64) && g.L[1] % (64 / g.L[0]) == 0;
 }
 
-StencilConfig default_config(const Geom &g, int prec, int ncol, int kind) {
+// The default in terms of bri_stencil_cfg (64-site tiles); the tuned table holds Brillouin launches
+// only, the Wilson stencil keeps the defaults.
+StencilConfig tile_config(const Geom &g, int prec, int ncol, int kind) {
     StencilConfig c;
-    // the tuned table holds Brillouin launches; the Wilson stencil keeps the defaults
-    if (kind == KERN_BRI && tuned_config(g, prec, ncol, &c)) return c;
     default_traversal(g, c);
     c.xcd_remap = 1;
     if (ncol >= 2) {
@@ -200,6 +219,112 @@ StencilConfig default_config(const Geom &g, int prec, int ncol, int kind) {
             c.xcd_remap = 1;
         }
     }
+    return c;
+}
+
+// Whole x-lines of at most 64 sites per wave.  Lines of 16, 32 or 64 sites fill the wave; other lengths
+// leave lanes idle (24-site lines: 48 of 64), and still win over 64-site tiles that cut the lines: the
+// x-neighbours come by lane moves, every load is one or a few full runs of sites, and the tile rows
+// form columns.  One right-hand side, before -> now: 24^3x48 FP64 1967 -> 1275 us, FP32 1298 -> 700;
+// 20x12x28x24 FP64 637 -> 300; 31x12x16x14 (extents whose only even tiles are 1 x 4 x 16 x 1) 879 -> 175;
+// 36x16x29x26 (36 of 64 lanes) 1675 -> 1200.  Below half the lanes the cut tiles stay.
+static bool lines_fit(const Geom &g, int *lines) {
+    if (g.L[0] > 64) return false;
+    int n = 64 / g.L[0];
+    if (n > g.L[1]) n = g.L[1];
+    if ((long long)line_tiles(g, n) * 32 > g.V) return false;
+    *lines = n;
+    return true;
+}
+
+// Columns of coly tile rows by colz z-planes: of the divisors, the cross-section with the smallest
+// halo (lines around it that are read with it) among those of at most `cap` tiles.
+static void line_columns(const Geom &g, int lines, int cap, StencilConfig &c) {
+    const int rows = (g.L[1] + lines - 1) / lines;
+    double best = 1e300;
+    for (int cz = 1; cz <= g.L[2] && cz <= cap; ++cz)
+        for (int cy = 1; cy <= rows && cy * cz <= cap; ++cy) {
+            if (g.L[2] % cz || rows % cy) continue;
+            const double halo = (cz + 2.0) * (cy * lines + 2.0) / ((double)cz * cy * lines);
+            if (halo < best) {
+                best = halo;
+                c.colz = cz;
+                c.coly = cy;
+            }
+        }
+}
+
+// Replaces the tile configuration by whole-line tiles where they measured faster.
+static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilConfig &c) {
+    int n = 0;
+    const bool fit = lines_fit(g, &n);
+    const int tiles = fit ? line_tiles(g, n) : g.V / 64;
+    // Few tiles: twelve waves on each (40 slabs in 4 turns instead of 10).  8^4, 64 tiles: 24 -> 22 us;
+    // at 12^4 (324 line tiles) four waves are faster (49 against 53 us).
+    const bool few = kind == KERN_BRI && ncol == 1 && tiles <= 256;
+    if (few) {
+        c.variant = VAR_STANDARD;
+        c.rpt = 0;
+        c.nsplit = 12;
+    }
+    if (!fit) return;
+    if (kind == KERN_BRI && ncol != 2 && xline_fits(g)) return;  // whole-line tiles already
+    // (16 x 4 tiles in columns one row wide: 16^4 overlap apply 4.02 ms, 4.15 in columns of 4 rows; the
+    // gradient's batches of 2 and 32 likewise, 13.3 against 13.5 ms; 3 right-hand sides gain, 312 -> 280 us)
+    if (kind == KERN_BRI && ncol != 3 && prec == BRI_F64 && tiles <= 1024 && c.colz > 0 && !few) return;
+    c.lines = n;
+    c.xcd_remap = 1;
+    if (kind == KERN_WIL) {
+        // the four one-hop slabs: 960 bytes of FP64 links and spinors a site, deep columns.  32^3x64
+        // FP64 755 -> 496 us, FP32 393 -> 312; 24^3x48 FP64 177 -> 166
+        if (ncol == 1) {
+            c.rpt = 0;
+            c.nsplit = g.V / 64 >= 8192 ? 2 : 4;
+        }
+        line_columns(g, n, 64, c);
+        return;
+    }
+    if (few) {
+        line_columns(g, n, 36, c);
+        return;
+    }
+    // One right-hand side per thread on the x-line kernel, or two (FP64) or three per thread on the
+    // standard kernel, which loads a link once for them but each neighbour spinor separately.  12
+    // right-hand sides at 24^3x48: FP64 12.5 ms (x-line) against 11.0 (R = 2), FP32 6.92 against
+    // 6.83 (R = 3); 3 right-hand sides at 20x12x28x24: FP64 705 us (x-line) against 772, FP32 374
+    // against 424.  Below 256 blocks the wider launch wins: 8^4, 4 right-hand sides 35 against 44 us.
+    c.variant = VAR_XLINE;
+    c.rpt = 0;
+    c.nsplit = 4;
+    const long long pair_blocks = (long long)tiles * ((ncol + 1) / 2);
+    if (prec == BRI_F64 && ncol >= 2 && ncol != 3 && pair_blocks >= 256) {
+        c.variant = VAR_STANDARD;
+        c.rpt = 2;
+    } else if (prec == BRI_F32 && ncol >= 9 && tiles >= 512) {
+        c.variant = VAR_STANDARD;
+        c.rpt = 3;
+    } else if (prec == BRI_F64 && ncol == 1 && tiles <= 1024) {
+        // up to a wave of blocks or two the shorter turns of the standard kernel (40 slabs in 10
+        // against 27 groups in 7) balance better: 12^3x24 82 against 91 us, 16^4 125 against 130
+        c.variant = VAR_STANDARD;
+    }
+    line_columns(g, n, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, c);
+}
+
+// Every launch leaves one pair of sums per tile; a tile holds at least 32 sites.
+int stencil_max_slots(const Geom &g) { return g.V / 32; }
+
+// the configuration a launch uses: the installed one, else the default with whole-line tiles where
+// bri_stencil_cfg cannot express them
+StencilConfig default_config(const Geom &g, int prec, int ncol, int kind) {
+    StencilConfig c;
+    if (kind == KERN_BRI && tuned_config(g, prec, ncol, &c)) return c;
+    return untuned_config(g, prec, ncol, kind);
+}
+
+StencilConfig untuned_config(const Geom &g, int prec, int ncol, int kind) {
+    StencilConfig c = tile_config(g, prec, ncol, kind);
+    lines_default(g, prec, ncol, kind, c);
     return c;
 }
 

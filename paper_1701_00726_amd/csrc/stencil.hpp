@@ -47,7 +47,7 @@ struct StencilArgs {
     int coly;     // column traversal width in tile rows along y (>= 1)
     int xcd_remap;
     int ncol;     // columns (right-hand sides); column c lives at offset c * 12 V
-    int nslots;   // partial-sum slots per column the reductions read (V / 64, one per 64-site tile,
+    int nslots;   // partial-sum slots per column the reductions read (one per tile,
                   // filled by the tile's block); a kernel with fewer blocks zeroes the slots it does
                   // not fill
     const void *W;
@@ -71,9 +71,10 @@ struct StencilConfig {
     int tile[4];    // 0 = automatic
     int colz;       // column traversal: z-planes per column (0 = lexicographic tiles)
     int coly = 0;   // column traversal: tile rows along y per column (0 = 1)
-    int nsplit;     // 1-RHS kernel: waves per 64-site tile (1, 2, 4)
+    int nsplit;     // 1-RHS kernel: waves per 64-site tile (1, 2, 4; 12 for VAR_STANDARD, defaults only)
     int rpt;        // multi-RHS kernel: right-hand sides per thread (0 = use the 1-RHS kernel)
     int xcd_remap;  // 1 = give each XCD a contiguous range of tiles
+    int lines = 0;    // see below
     int variant = 0;  // 1-RHS kernel variant (rpt must be 0 for 1 and 2):
                       //   VAR_STANDARD  the 64-site tile kernel above;
                       //   VAR_TSTREAM   t-streaming: xyz tile tile[0..2] (256 sites), chunks of
@@ -84,6 +85,10 @@ struct StencilConfig {
                       //   VAR_MFMA      FP32 / bfloat16 links only: rpt (1..4) right-hand sides
                       //                 per thread, the colour transport on the matrix cores
 };
+
+// StencilConfig::lines > 0 replaces the tile by `lines` whole x-lines (at most 64 sites, lines * L_x, the
+// last tile row along y possibly with fewer) in the columns of colz and coly, for lattices whose
+// x-lines do not fill a wave's 64 lanes evenly; set by default_config only.
 
 enum StencilVariant { VAR_STANDARD = 0, VAR_TSTREAM = 1, VAR_XLINE = 2, VAR_MFMA = 3 };
 
@@ -96,8 +101,13 @@ bool tuned_config(const Geom &g, int prec, int ncol, StencilConfig *out);
 int geom_check(const bri_geom *geom, Geom *g);
 int plan_tile(const Geom &g, const StencilConfig &cfg, int tile[4], int nb[4]);
 StencilConfig default_config(const Geom &g, int prec, int ncol, int kind = KERN_BRI);
+// the default without the table; and in terms of bri_stencil_cfg (64-site tiles) only
+StencilConfig untuned_config(const Geom &g, int prec, int ncol, int kind);
+StencilConfig tile_config(const Geom &g, int prec, int ncol, int kind);
 int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilConfig &cfg, hipStream_t st);
 
-inline int stencil_blocks(const Geom &g) { return g.V / 64; }
+// partial-sum slots per column a launch with cfg fills, and the most any configuration fills
+int stencil_slots(const Geom &g, const StencilConfig &cfg);
+int stencil_max_slots(const Geom &g);
 
 }  // namespace bri

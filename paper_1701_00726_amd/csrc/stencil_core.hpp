@@ -173,10 +173,13 @@ __device__ __forceinline__ void transport_reg(C (&chi)[4][3], const C (&w)[3][3]
 //              z.  A tile's neighbours in y, z and t are then 1, coly and
 //              coly * colz tiles away: tiles an XCD runs together hold most stencil
 //              neighbours of each other, so the second read of a link (by the
-//              partner site) and re-read spinors stay in that XCD's L2.
+//              partner site) and re-read spinors stay in that XCD's L2.  Such a tile may
+//              hold fewer than 64 sites (tile[0] * tile[1] < 64) and the last tile row along
+//              y fewer lines: the lanes without a site get one of the tile's and live = false.
 __device__ __forceinline__ unsigned tile_site(const Geom &g, const int tile[4], const int nb[4], int colz, int coly,
-                                              int blk, int lane, unsigned om[4], unsigned o0[4], unsigned op[4]) {
+                                              int blk, int lane, unsigned om[4], unsigned o0[4], unsigned op[4], bool &live) {
     int c[4];
+    live = true;
     if (colz > 0) {
         const int per_col = coly * colz * g.L[3];
         const int col = blk / per_col, rem = blk - col * per_col;
@@ -185,8 +188,10 @@ __device__ __forceinline__ unsigned tile_site(const Geom &g, const int tile[4], 
         const int ncy = nb[1] / coly;
         const int cx = col % nb[0], r2 = col / nb[0];
         const int cy = r2 % ncy, cz = r2 / ncy;
-        c[0] = cx * tile[0] + lane % tile[0];
-        c[1] = (cy * coly + yy) * tile[1] + lane / tile[0];
+        const int line = lane / tile[0], row = (cy * coly + yy) * tile[1];
+        live = line < tile[1] && row + line < g.L[1];
+        c[0] = cx * tile[0] + lane - line * tile[0];
+        c[1] = live ? row + line : row;
         c[2] = cz * colz + zt;
         c[3] = tt;
     } else {
@@ -214,8 +219,13 @@ __device__ __forceinline__ unsigned tile_site(const Geom &g, const int tile[4], 
     return o0[0] + o0[1] + o0[2] + o0[3];
 }
 
+// Launch order -> logical block with remap: consecutive blocks go to the 8 XCDs in turn, so XCD k gets
+// the blocks k, k + 8, ...; numbering those consecutively gives each XCD one contiguous range (the first
+// nblk % 8 XCDs one block more).
 __device__ __forceinline__ int xcd_order(int blk, int nblk, int remap) {
-    return (remap && (nblk & 7) == 0) ? (blk & 7) * (nblk >> 3) + (blk >> 3) : blk;
+    if (!remap) return blk;
+    const int k = blk & 7, more = nblk & 7;
+    return k * (nblk >> 3) + (k < more ? k : more) + (blk >> 3);
 }
 
 // Tile and column group of this block.  The column groups (one column, or R of them) of a tile are

@@ -95,13 +95,51 @@ template <int MODE> __device__ __forceinline__ bool col_done(const StencilArgs &
     return false;
 }
 
+// The NSPLIT partial sums of a tile meet in LDS; wave q < 4 gets components q NCOMP, ..., summed over the
+// waves in order.  Twelve waves exchange four components (48 KB in double precision) at a time.
+template <int NSPLIT, int NCOMP, typename C>
+__device__ __forceinline__ void combine(C (&res)[NCOMP], const C (&acc)[4][3], int q, int lane) {
+    if constexpr (NSPLIT == 1) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) res[c] = acc[c / 3][c % 3];
+    } else {
+        constexpr int ROUNDS = NSPLIT > 4 ? NCOMP : 1, PER = 12 / ROUNDS;
+        __shared__ C red[NSPLIT][PER][64];
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) {
+            // component of wave w in this round, for ROUNDS > 1: w NCOMP + r; else all twelve
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int comp = ROUNDS > 1 ? i * NCOMP + r : i;
+                red[q][i][lane] = acc[comp / 3][comp % 3];
+            }
+            __syncthreads();
+            if (NSPLIT <= 4 || q < 4) {
+#pragma unroll
+                for (int i = 0; i < (ROUNDS > 1 ? 1 : NCOMP); ++i) {
+                    const int slot = ROUNDS > 1 ? q : q * NCOMP + i;
+                    C v = red[0][slot][lane];
+#pragma unroll
+                    for (int w = 1; w < NSPLIT; ++w) {
+                        const C u = red[w][slot][lane];
+                        v.x += u.x;
+                        v.y += u.y;
+                    }
+                    res[ROUNDS > 1 ? r : i] = v;
+                }
+            }
+            if (r + 1 < ROUNDS) __syncthreads();
+        }
+    }
+}
+
 // ------------------------------------------------------- one right-hand side
 
 template <class LS, int NSPLIT, bool DAG, int MODE, int KIND>
 __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     using R = typename LS::R;
     using C = typename Cx<R>::T;
-    constexpr int NCOMP = 12 / NSPLIT;
+    constexpr int NFIN = NSPLIT > 4 ? 4 : NSPLIT, NCOMP = 12 / NFIN;
     int blk, col;
     tile_and_group(a.nslots, a.xcd_remap, blk, col);
     if (col >= a.ncol || col_done<MODE>(a, col)) return;  // whole block: this column has converged
@@ -110,7 +148,8 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     const int lane = threadIdx.x & 63;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned om[4], o0[4], op[4];
-    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op);
+    bool site;  // this lane has a site of its own
+    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op, site);
 
     const C *__restrict__ in = (const C *)a.in + (size_t)col * 12 * V;
     const typename LS::store_t *__restrict__ W = (const typename LS::store_t *)a.W;
@@ -145,41 +184,19 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     }
 
     // combine the NSPLIT partial sums through LDS
-    __shared__ C red[NSPLIT > 1 ? NSPLIT : 1][12][64];
     __shared__ double wsum[NSPLIT][2];
     C res[NCOMP];
-    if constexpr (NSPLIT > 1) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) red[q][s * 3 + b][lane] = acc[s][b];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NCOMP; ++i) {
-            const int comp = q * NCOMP + i;
-            C v = red[0][comp][lane];
-#pragma unroll
-            for (int w = 1; w < NSPLIT; ++w) {
-                const C u = red[w][comp][lane];
-                v.x += u.x;
-                v.y += u.y;
-            }
-            res[i] = v;
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) res[s * 3 + b] = acc[s][b];
-    }
+    combine<NSPLIT>(res, acc, q, lane);
+    if (q >= NFIN) site = false;  // (waves beyond the first four hold no component)
 
-    if (a.g.csw != 0.0) {
+    if (a.g.csw != 0.0 && q < NFIN) {
 #pragma unroll
         for (int i = 0; i < NCOMP; ++i) clover_row<LS>(res[i], W + (size_t)LINK_SLAB_ENTRIES * V, in, q * NCOMP + i, x, V);
     }
     double n0 = 0.0, n1 = 0.0;
 #pragma unroll
-    for (int i = 0; i < NCOMP; ++i) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
+    for (int i = 0; i < NCOMP; ++i)
+        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
     if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
         // deterministic: wave sums, then the NSPLIT wave totals in order
         n0 = wave_sum(n0);
@@ -248,7 +265,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
     using R = typename LS::R;
     using C = typename Cx<R>::T;
     using S = typename LS::store_t;
-    constexpr int NCOMP = 12 / NSPLIT;
+    constexpr int NFIN = NSPLIT > 4 ? 4 : NSPLIT, NCOMP = 12 / NFIN;
     int blk, col;
     tile_and_group(a.nslots, a.xcd_remap, blk, col);
     if (col >= a.ncol || col_done<MODE>(a, col)) return;
@@ -257,7 +274,8 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
     const int lane = threadIdx.x & 63;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned om[4], o0[4], op[4];
-    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op);
+    bool site;  // this lane has a site of its own
+    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op, site);
     const int tx = a.tile[0];  // = L_x
     const int lx = lane % tx;
     const int lane_m = lane - lx + (lx == 0 ? tx - 1 : lx - 1);  // holds x - 1 (periodic in x)
@@ -312,40 +330,18 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
         }
     }
 
-    __shared__ C red[NSPLIT > 1 ? NSPLIT : 1][12][64];
     __shared__ double wsum[NSPLIT][2];
     C res[NCOMP];
-    if constexpr (NSPLIT > 1) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) red[q][s * 3 + b][lane] = acc[s][b];
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < NCOMP; ++i) {
-            const int comp = q * NCOMP + i;
-            C v = red[0][comp][lane];
-#pragma unroll
-            for (int w = 1; w < NSPLIT; ++w) {
-                const C u = red[w][comp][lane];
-                v.x += u.x;
-                v.y += u.y;
-            }
-            res[i] = v;
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int b = 0; b < 3; ++b) res[s * 3 + b] = acc[s][b];
-    }
-    if (a.g.csw != 0.0) {
+    combine<NSPLIT>(res, acc, q, lane);
+    if (q >= NFIN) site = false;  // (waves beyond the first four hold no component)
+    if (a.g.csw != 0.0 && q < NFIN) {
 #pragma unroll
         for (int i = 0; i < NCOMP; ++i) clover_row<LS>(res[i], W + (size_t)LINK_SLAB_ENTRIES * V, in, q * NCOMP + i, x, V);
     }
     double n0 = 0.0, n1 = 0.0;
 #pragma unroll
-    for (int i = 0; i < NCOMP; ++i) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
+    for (int i = 0; i < NCOMP; ++i)
+        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
     if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
         n0 = wave_sum(n0);
         n1 = wave_sum(n1);
@@ -394,7 +390,8 @@ __global__ __launch_bounds__(64 * MRHS_SPLIT) void stencil_xline_mrhs_kernel(Ste
     if (!any) return;
 
     unsigned om[4], o0[4], op[4];
-    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op);
+    bool site;  // this lane has a site of its own
+    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op, site);
     const int tx = a.tile[0];  // = L_x
     const int lx = lane % tx;
     const int lane_m = lane - lx + (lx == 0 ? tx - 1 : lx - 1);
@@ -477,7 +474,7 @@ __global__ __launch_bounds__(64 * MRHS_SPLIT) void stencil_xline_mrhs_kernel(Ste
             }
             if (a.g.csw != 0.0)
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
-            epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
+            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
         }
         if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
             n0 = wave_sum(n0);
@@ -688,7 +685,8 @@ void stencil_mrhs_kernel(StencilArgs a) {
     if (!any) return;
 
     unsigned om[4], o0[4], op[4];
-    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op);
+    bool site;  // this lane has a site of its own
+    const unsigned x = tile_site(a.g, a.tile, a.nb, a.colz, a.coly, blk, lane, om, o0, op, site);
     const C *__restrict__ in = (const C *)a.in + (size_t)col0 * 12 * V;
     const typename LS::store_t *__restrict__ W = (const typename LS::store_t *)a.W;
 
@@ -761,7 +759,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
             }
             if (a.g.csw != 0.0)
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
-            epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
+            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
         }
         if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
             // deterministic: wave sums, then the NSPLIT wave totals in order
@@ -950,6 +948,7 @@ inline hipError_t launch_cfg(const StencilArgs &a, int mode, const StencilConfig
         case 1: return launch_1rhs<LS, 1, DAG, KIND>(a, mode, st);
         case 2: return launch_1rhs<LS, 2, DAG, KIND>(a, mode, st);
         case 4: return launch_1rhs<LS, 4, DAG, KIND>(a, mode, st);
+        case 12: return launch_1rhs<LS, 12, DAG, KIND>(a, mode, st);
         default: return hipErrorInvalidValue;
         }
     case 1: return launch_mrhs<LS, 1, DAG, KIND>(a, mode, st);

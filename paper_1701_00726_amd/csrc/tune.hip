@@ -195,9 +195,14 @@ int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, 
     if (rc != BRI_OK) return rc;
     if (!W || !in || !out || nrhs < 1 || reps < 1 || g.V % 64) return BRI_EINVAL;
     if (prec != BRI_F64 && prec != BRI_F32 && prec != BRI_F32_BF16W) return BRI_EINVAL;
-    double bus = 1e300;
-    StencilConfig bc{};
-    bool found = false;
+    // the default first: it may be a whole-line launch that bri_stencil_cfg cannot express, and stays
+    // (nothing installed) if no candidate beats it
+    StencilConfig bc = tile_config(g, prec, nrhs, KERN_BRI);
+    double bus = 0.0;
+    rc = time_config(g, W, prec, in, out, nrhs, untuned_config(g, prec, nrhs, KERN_BRI), reps, (hipStream_t)stream, &bus);
+    if (rc == BRI_EINVAL) bus = 1e300;
+    if (rc != BRI_OK && rc != BRI_EINVAL) return rc;
+    bool keep = rc == BRI_OK, found = keep;
     for (const StencilConfig &c : candidates(g, prec, nrhs)) {
         double us = 0.0;
         rc = time_config(g, W, prec, in, out, nrhs, c, reps, (hipStream_t)stream, &us);
@@ -207,12 +212,16 @@ int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, 
             bus = us;
             bc = c;
             found = true;
+            keep = false;
         }
     }
     if (!found) return BRI_EINVAL;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tuned[key_of(g, prec, nrhs)] = bc;
+        if (keep)
+            g_tuned.erase(key_of(g, prec, nrhs));
+        else
+            g_tuned[key_of(g, prec, nrhs)] = bc;
     }
     if (best) *best = to_public(bc);
     if (best_us) *best_us = bus;
@@ -247,7 +256,9 @@ int bri_get_stencil_cfg(const bri_geom *geom, int prec, int nrhs, bri_stencil_cf
     int rc = geom_check(geom, &g);
     if (rc != BRI_OK) return rc;
     if (!cfg || nrhs < 1) return BRI_EINVAL;
-    *cfg = to_public(default_config(g, prec, nrhs));
+    StencilConfig c;
+    if (!tuned_config(g, prec, nrhs, &c)) c = tile_config(g, prec, nrhs, KERN_BRI);
+    *cfg = to_public(c);
     return BRI_OK;
 }
 

@@ -1,0 +1,87 @@
+"""Launches on tiles of whole x-lines that do not fill a wave's 64 lanes, or a tile row that does not
+divide L_y, and the twelve-wave launch of small lattices: the Brillouin and Wilson operators, their
+adjoints and the solver epilogues against the oracle (App. C.1 stencil, eq. (def_wils), Sec. 3.3).
+
+Tolerances: the operator is a sum of 81 terms of 3 products with weights summing to about 4, so a
+relative L2 error of a few units of roundoff: 1e-14 in FP64 (45 eps), 2e-6 in FP32 (17 eps); the
+overlap apply carries its CG tolerance 1e-12 and is held to 1e-10."""
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1701_00726_amd as bri
+import synth
+from tests._gpu import need_gpu, rel_l2, round_links
+
+pytestmark = pytest.mark.gpu
+
+LATTICES = [
+    (20, 7, 8, 16),  # 3 lines a tile (60 lanes), the last tile row holds one
+    (33, 4, 8, 16),  # 1 line a tile, 33 lanes
+    (24, 12, 6, 12),  # 2 lines a tile (48 lanes), columns of several tile rows and planes
+    (9, 8, 8, 8),  # 7 lines, then 1; twelve waves a tile
+    (64, 3, 4, 4),  # full waves, twelve waves a tile
+    (5, 4, 4, 8),  # 20 of 64 lanes would be used: cut 64-site tiles, twelve waves
+]
+
+
+@pytest.fixture(scope="module")
+def fields():
+    out = {}
+    for L in LATTICES:
+        U = synth.random_links(L, 0.6, 5100 + L[0])
+        out[L] = (bri.links_to_device(U), oracle.links(L, U))
+    return out
+
+
+@pytest.mark.parametrize("L", LATTICES)
+@pytest.mark.parametrize("prec,tol", [(bri.F64, 1e-14), (bri.F32, 2e-6), (bri.F32_BF16W, 2e-6)])
+def test_line_tiles_match_oracle(fields, L, prec, tol):
+    need_gpu()
+    Ud, Wo = fields[L]
+    W = bri.build_links(L, Ud, prec)
+    Wr = round_links(Wo, prec)
+    print(f"[lines] {L} prec {prec}", flush=True)
+    for nrhs in (1, 2, 3, 5, 9):
+        psi = synth.gaussian_source(L, 5200 + nrhs, nrhs=nrhs).astype(np.complex64 if prec else np.complex128)
+        x = bri.spinor_to_device(psi.astype(np.complex128), prec)
+        got, gotd = (bri.spinor_to_host(f(L, W, prec, -0.9, x)) for f in (bri.apply, bri.apply_dag))
+        ref = oracle.dirac(L, Wr, -0.9, psi.astype(np.complex128))
+        refd = oracle.dirac_adj(L, Wr, -0.9, psi.astype(np.complex128))
+        for r in range(nrhs):
+            assert rel_l2(got[r], ref[r]) < tol, (nrhs, r)
+            assert rel_l2(gotd[r], refd[r]) < tol, (nrhs, r)
+
+
+@pytest.mark.parametrize("L", LATTICES)
+def test_line_tiles_wilson(fields, L):
+    need_gpu()
+    Ud, _ = fields[L]
+    K = oracle.WilsonKernel(np.transpose(Ud.cpu().numpy(), (0, 3, 1, 2)))
+    W = bri.build_links(L, Ud, bri.F64)
+    print(f"[lines] wilson {L}", flush=True)
+    for nrhs in (1, 4):
+        psi = synth.gaussian_source(L, 5300 + nrhs, nrhs=nrhs)
+        x = bri.spinor_to_device(psi)
+        got = bri.spinor_to_host(bri.wilson_apply(L, W, bri.F64, -0.8, x))
+        gotd = bri.spinor_to_host(bri.wilson_apply_dag(L, W, bri.F64, -0.8, x))
+        for r in range(nrhs):
+            assert rel_l2(got[r], oracle.dirac(L, K, -0.8, psi[r])) < 1e-14, r
+            assert rel_l2(gotd[r], oracle.dirac_adj(L, K, -0.8, psi[r])) < 1e-14, r
+
+
+@pytest.mark.parametrize("L,nrhs", [((20, 7, 4, 8), 1), ((20, 7, 4, 8), 4), ((9, 8, 8, 8), 1), ((33, 4, 4, 8), 3)])
+def test_line_tiles_in_the_solver(L, nrhs):
+    """The norm and residual epilogues: one pair of partial sums per tile, idle lanes adding nothing."""
+    need_gpu()
+    U = synth.smeared_links(L, 0.5, 5400, 0.6, 1)
+    W = bri.build_links(L, bri.links_to_device(U), bri.F64)
+    Wo = oracle.links(L, U)
+    b = synth.gaussian_source(L, 5401, nrhs=nrhs)
+    print(f"[lines] overlap {L} {nrhs}", flush=True)
+    out, _ = bri.OverlapOp(L, W, kl_n=6, tol=1e-12, nrhs=nrhs).apply(bri.spinor_to_device(b))
+    got = bri.spinor_to_host(out)
+    for r in range(nrhs):
+        ref, _, _ = oracle.ov_apply(L, Wo, 1.0, 6, b[r], tol=1e-13)
+        assert rel_l2(got[r], ref) < 1e-10, r
