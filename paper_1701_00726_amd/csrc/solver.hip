@@ -58,6 +58,10 @@
 namespace bri {
 
 constexpr int RED_THREADS = 256;
+// Threads of the alpha / beta kernels' one block per column from RED_WIDE_SLOTS partial sums on (one
+// block is bound by the latency of its loads): 27648 sums of 12 columns 20 -> 8.7 us (alpha), 24 -> 13
+// (beta); below, more waves only cost barriers.
+constexpr int RED_WIDE = 1024, RED_WIDE_SLOTS = 4096;
 constexpr int CHECK_EVERY = 8;
 constexpr double LONG_ITER_SEC = 2e-3;  // iterations this long are polled one by one before the switch
 constexpr int INIT_BLOCKS = 256;  // vector-kernel blocks per column
@@ -68,13 +72,26 @@ constexpr int INIT_BLOCKS = 256;  // vector-kernel blocks per column
 // each wave folds its lanes with shuffles, and every thread adds the wave sums in the same order,
 // so all threads return the same (x, y) = (sum of component 0, sum of component 1)
 static_assert(RED_THREADS % 64 == 0 && MAXS <= RED_THREADS, "one thread per shift");
-__device__ double2 block_sum2(const double *partial, int n) {
-    __shared__ double2 sh[RED_THREADS / 64];
-    double sx = 0.0, sy = 0.0;
-    for (int i = threadIdx.x; i < n; i += RED_THREADS) {
-        sx += partial[2 * i];
-        sy += partial[2 * i + 1];
+template <int T> __device__ double2 block_sum2(const double *partial, int n) {
+    __shared__ double2 sh[T / 64];
+    const double2 *__restrict__ pp = (const double2 *)partial;
+    // four independent slices in flight
+    double2 s[4] = {};
+    int i = threadIdx.x;
+    for (; i + 3 * T < n; i += 4 * T) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double2 v = pp[i + k * T];
+            s[k].x += v.x;
+            s[k].y += v.y;
+        }
     }
+    for (; i < n; i += T) {
+        const double2 v = pp[i];
+        s[0].x += v.x;
+        s[0].y += v.y;
+    }
+    double sx = (s[0].x + s[1].x) + (s[2].x + s[3].x), sy = (s[0].y + s[1].y) + (s[2].y + s[3].y);
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         sx += __shfl_down(sx, off, 64);
@@ -84,7 +101,7 @@ __device__ double2 block_sum2(const double *partial, int n) {
     __syncthreads();
     double2 t = sh[0];
 #pragma unroll
-    for (int w = 1; w < RED_THREADS / 64; ++w) {
+    for (int w = 1; w < T / 64; ++w) {
         t.x += sh[w].x;
         t.y += sh[w].y;
     }
@@ -163,7 +180,7 @@ __global__ void ms_init_kernel(size_t n, const B *__restrict__ b, C *__restrict_
 // one block per column
 __global__ void ms_scalar_init_kernel(ColState *states, const double *partial, int nblk, double tol) {
     ColState *st = states + blockIdx.x;
-    const double b2 = block_sum2(partial + 2 * (size_t)blockIdx.x * nblk, nblk).x;
+    const double b2 = block_sum2<RED_THREADS>(partial + 2 * (size_t)blockIdx.x * nblk, nblk).x;
     if (threadIdx.x == 0) {
         st->bnorm2 = b2;
         st->rr = b2;
@@ -195,10 +212,11 @@ __global__ void ms_scalar_init_kernel(ColState *states, const double *partial, i
 
 // alpha and the shifted alpha^sigma after t = X p (partials: |t|^2, |p|^2).  Every thread forms
 // alpha from the same sums; thread i < nshift updates shift i, thread 0 the column scalars.
-__global__ void ms_alpha_kernel(ColState *states, const double *partial, int nblk) {
+template <int T>
+__global__ __launch_bounds__(T) void ms_alpha_kernel(ColState *states, const double *partial, int nblk) {
     ColState *st = states + blockIdx.x;
     if (st->done) return;
-    const double2 sums = block_sum2(partial + 2 * (size_t)blockIdx.x * nblk, nblk);
+    const double2 sums = block_sum2<T>(partial + 2 * (size_t)blockIdx.x * nblk, nblk);
     const double pAp = sums.x + st->sigma0 * sums.y;
     const double alpha = st->rr / pAp;
     const bool bad = !isfinite(alpha) || pAp <= 0.0;
@@ -231,10 +249,14 @@ __global__ void ms_alpha_kernel(ColState *states, const double *partial, int nbl
 // Stopping: shift i by itself once |r_i| <= tol_i |b|; with the result bound (joint), shift i
 // once ebw_i |r_i| <= tol |b| / (2 nshift), and every shift once sum_i ebw_i |r_i| <= tol |b|
 // (a stopped shift counts with its residual when it stopped).
-__global__ void ms_beta_kernel(ColState *states, const double *partial, int nblk, WinState *ws, int xmode) {
+template <int T>
+__global__ __launch_bounds__(T) void ms_beta_kernel(ColState *states, const double *partial, int nblk, WinState *ws, int xmode) {
     ColState *st = states + blockIdx.x;
-    if (st->done) return;
-    const double rr_new = block_sum2(partial + 2 * (size_t)blockIdx.x * nblk, nblk).x;
+    if (st->done) {
+        if (st->done == 2 && threadIdx.x == 0) st->done = 1;  // its last vector update ran an iteration ago
+        return;
+    }
+    const double rr_new = block_sum2<T>(partial + 2 * (size_t)blockIdx.x * nblk, nblk).x;
     const bool bad = !isfinite(rr_new);
     const double beta = rr_new / st->rr;
     const int it = st->iter + 1;
@@ -297,12 +319,19 @@ __global__ void ms_beta_kernel(ColState *states, const double *partial, int nblk
                 if (step)
                     for (int j = 1; j <= m; ++j) w->h[i][j] += wgt * w->c[i][j];
             } else {
-                for (int j = 1; j <= m; ++j) {
-                    double v = i < ns ? wgt * w->c[i][j] : 0.0;
+                // eight sums over the shifts at once: lane i puts its terms in LDS, lane 8 (j - 1) + k
+                // adds those of shifts k, k + 8, ..., and eight lanes meet in three exchanges
+                __shared__ double terms[MAXS][WIN + 1];
+                if (i < ns)
+                    for (int j = 1; j <= m; ++j) terms[i][j] = wgt * w->c[i][j];
+                __builtin_amdgcn_wave_barrier();
+                const int j = (i >> 3) + 1;
+                double v = 0.0;
+                if (j <= m)
+                    for (int k = i & 7; k < ns; k += 8) v += terms[k][j];
 #pragma unroll
-                    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                    if (i == 0) w->f[j] += v;
-                }
+                for (int off = 4; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+                if (j <= m && (i & 7) == 0) w->f[j] += v;
             }
             // p^sigma <- zeta_{k+1} r_{k+1} + beta^sigma p^sigma for the shifts still running;
             // the base direction p <- r_{k+1} + beta p always
@@ -575,7 +604,8 @@ __global__ void ms_window_reset_kernel(WinState *ws) {
     if (i == 0) w->wn = 0;
 }
 
-// done 2 -> 1 for every column; *alldone = 1 once every column is done, else 2 when sw2 > 0 and
+// At the end of a polling block: done 2 -> 1 for every column (an iteration inside the block does so
+// for the columns that stopped in the one before it, in ms_beta_kernel); *alldone = 1 once every column is done, else 2 when sw2 > 0 and
 // every column still iterating has |r|^2 <= sw2 |b|^2 (time for the low-precision phase), else 0
 __global__ void ms_finish_kernel(ColState *states, int ncol, int *alldone, double sw2) {
     __shared__ int cnt[256], low[256];
@@ -961,13 +991,22 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
                               : Phase{}};
     const double sw2 = has_lo ? s.lo_switch * s.lo_switch : 0.0;
 
-    // one CG iteration for every column: t = X p, alpha, r update, beta, vector updates, done flags
+    // one CG iteration for every column: t = X p, alpha, r update, beta, vector updates
     auto iteration = [&](const Phase &ph, bool lo, hipStream_t q) -> int {
+        const bool wide = ph.nslots >= RED_WIDE_SLOTS;
         const int e1 = stencil_launch(ph.a1, ph.prec, false, EPI_NORMS, ph.cfg, q);
-        hipLaunchKernelGGL(ms_alpha_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, ph.nslots);
+        if (wide)
+            hipLaunchKernelGGL(ms_alpha_kernel<RED_WIDE>, dim3(s.ncol), dim3(RED_WIDE), 0, q, s.st, s.partial, ph.nslots);
+        else
+            hipLaunchKernelGGL(ms_alpha_kernel<RED_THREADS>, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial,
+                               ph.nslots);
         const int e2 = stencil_launch(ph.a2, ph.prec, true, EPI_CG_R, ph.cfg, q);
-        hipLaunchKernelGGL(ms_beta_kernel, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial, ph.nslots,
-                           s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
+        if (wide)
+            hipLaunchKernelGGL(ms_beta_kernel<RED_WIDE>, dim3(s.ncol), dim3(RED_WIDE), 0, q, s.st, s.partial, ph.nslots,
+                               s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
+        else
+            hipLaunchKernelGGL(ms_beta_kernel<RED_THREADS>, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial,
+                               ph.nslots, s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
         if (s.windowed && !lo)
             hipLaunchKernelGGL((ms_pupdate_kernel<double2>), ugrid, dim3(256), 0, q, s.st, s.ws, n, s.ncol,
                                (const double2 *)ph.r, (double2 *)ph.p, (double2 *)ph.R);
@@ -982,7 +1021,6 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
             hipLaunchKernelGGL((ms_update_kernel<float2, double2>), ugrid, dim3(256), 0, q, s.st, n, s.ncol,
                                (const float2 *)ph.r, (float2 *)ph.p, (double2 *)s.y, (double2 *)s.x,
                                (float2 *)ph.ps);
-        hipLaunchKernelGGL(ms_finish_kernel, dim3(1), dim3(256), 0, q, s.st, s.ncol, s.alldone, lo ? 0.0 : sw2);
         if (e1 != BRI_OK || e2 != BRI_OK) return e1 != BRI_OK ? e1 : e2;
         return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
     };
@@ -1086,6 +1124,11 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         const int it_before = it;
         const Phase &ph = phases[phase];
         const bool lo = phase == 1;
+        // the flags the host polls, once per polling block
+        auto finish = [&](hipStream_t q) -> int {
+            hipLaunchKernelGGL(ms_finish_kernel, dim3(1), dim3(256), 0, q, s.st, s.ncol, s.alldone, lo ? 0.0 : sw2);
+            return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
+        };
         // one iteration, then the fold whenever the window is full (every WIN iterations)
         auto step = [&](int &sf, bool &fw, hipStream_t q) -> int {
             int e = iteration(ph, lo, q);
@@ -1109,7 +1152,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
                         const int e = step(sf, fw, q);
                         if (e != BRI_OK) return e;
                     }
-                    return BRI_OK;
+                    return finish(q);
                 },
                 strm, &captured);
             if (rc != BRI_OK) return rc;
@@ -1123,6 +1166,8 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
                 const int e = step(since_fold, first_window, strm);
                 if (e != BRI_OK) return e;
             }
+            const int e = finish(strm);
+            if (e != BRI_OK) return e;
         }
         BRI_HIP_CHECK(hipMemcpyAsync(hflag, s.alldone, sizeof(int), hipMemcpyDeviceToHost, strm));
         BRI_HIP_CHECK(hipStreamSynchronize(strm));
