@@ -219,15 +219,6 @@ __device__ __forceinline__ unsigned tile_site(const Geom &g, const int tile[4], 
     return o0[0] + o0[1] + o0[2] + o0[3];
 }
 
-// Launch order -> logical block with remap: consecutive blocks go to the 8 XCDs in turn, so XCD k gets
-// the blocks k, k + 8, ...; numbering those consecutively gives each XCD one contiguous range (the first
-// nblk % 8 XCDs one block more).
-__device__ __forceinline__ int xcd_order(int blk, int nblk, int remap) {
-    if (!remap) return blk;
-    const int k = blk & 7, more = nblk & 7;
-    return k * (nblk >> 3) + (k < more ? k : more) + (blk >> 3);
-}
-
 // Tile and column group of this block.  The column groups (one column, or R of them) of a tile are
 // consecutive along x, gridDim.x / ntiles of them (all, unless grid.x would grow too large, the
 // rest follow in blockIdx.y), so that after the XCD ordering the blocks that read the same links
