@@ -90,7 +90,7 @@ int plan_tile(const Geom &g, const StencilConfig &cfg, int tile[4], int nb[4]) {
 static int line_tiles(const Geom &g, int n) { return (g.L[1] + n - 1) / n * g.L[2] * g.L[3]; }
 
 int stencil_slots(const Geom &g, const StencilConfig &cfg) {
-    return cfg.lines > 0 ? line_tiles(g, cfg.lines) : g.V / 64;
+    return cfg.small > 0 ? g.V / 16 : cfg.lines > 0 ? line_tiles(g, cfg.lines) : g.V / 64;
 }
 
 int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilConfig &cfg, hipStream_t st) {
@@ -105,7 +105,7 @@ int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilCon
         a.nb[1] = (a.g.L[1] + n - 1) / n;
         a.nb[2] = a.g.L[2];
         a.nb[3] = a.g.L[3];
-    } else {
+    } else if (cfg.small == 0) {
         rc = plan_tile(a.g, cfg, a.tile, a.nb);
     }
     if (rc != BRI_OK) return rc;
@@ -222,6 +222,8 @@ StencilConfig tile_config(const Geom &g, int prec, int ncol, int kind) {
     return c;
 }
 
+constexpr int SMALL_MAX_SITES = 16 * 1536;  // the small-lattice kernel's blocks of 16 sites
+
 // Whole x-lines of at most 64 sites per wave.  Lines of 16, 32 or 64 sites fill the wave; other lengths
 // leave lanes idle (24-site lines: 48 of 64), and still win over 64-site tiles that cut the lines: the
 // x-neighbours come by lane moves, every load is one or a few full runs of sites, and the tile rows
@@ -254,14 +256,26 @@ static void line_columns(const Geom &g, int lines, int cap, StencilConfig &c) {
         }
 }
 
-// Replaces the tile configuration by whole-line tiles where they measured faster.
+// Replaces the tile configuration by the small-lattice kernel or whole-line tiles where they measured
+// faster.
 static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilConfig &c) {
+    // Up to about a block per CU (two in FP64 batches, six in FP32 and with bfloat16 links) of the small-
+    // lattice kernel, eight waves each up to 256 blocks: 8^4 FP64 21.6 -> 15.5 us, FP32 16.7 -> 7.1,
+    // bfloat16 links 14.3 -> 6.8; 4^4 x 6 FP64 33.5 -> 9.6.  Beyond, its blocks queue and the tile
+    // kernels' shared loads win: FP64 8x8x8x16 24.0 against 22.5 us, 8^4 x 3 35 against 29; FP32
+    // 8x8x8x16 x 6 51 against 39, 12^4 x 2 48 against 46.
+    const long long blocks16 = (long long)g.V / 16 * ncol;
+    if (kind == KERN_BRI && g.V <= SMALL_MAX_SITES && blocks16 <= (prec != BRI_F64 ? 1536 : ncol > 1 ? 512 : 256)) {
+        c.small = blocks16 <= 256 ? 8 : 4;
+        c.xcd_remap = 1;
+        return;
+    }
     int n = 0;
     const bool fit = lines_fit(g, &n);
     const int tiles = fit ? line_tiles(g, n) : g.V / 64;
-    // Few tiles: twelve waves on each (40 slabs in 4 turns instead of 10).  8^4, 64 tiles: 24 -> 22 us;
-    // at 12^4 (324 line tiles) four waves are faster (49 against 53 us).
-    const bool few = kind == KERN_BRI && ncol == 1 && tiles <= 256;
+    // FP64, one right-hand side, up to 256 tiles: twelve waves on each (40 slabs in 4 turns instead of
+    // 10), 8x8x8x16 31 -> 22.5 us; at 12^4 (324 line tiles) four waves are faster (49 against 53 us).
+    const bool few = kind == KERN_BRI && prec == BRI_F64 && ncol == 1 && tiles <= 256;
     if (few) {
         c.variant = VAR_STANDARD;
         c.rpt = 0;
@@ -311,8 +325,9 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     line_columns(g, n, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, c);
 }
 
-// Every launch leaves one pair of sums per tile; a tile holds at least 32 sites.
-int stencil_max_slots(const Geom &g) { return g.V / 32; }
+// Every launch leaves one pair of sums per tile; a tile holds at least 32 sites, 16 in the small-lattice
+// kernel.
+int stencil_max_slots(const Geom &g) { return g.V <= SMALL_MAX_SITES ? g.V / 16 : g.V / 32; }
 
 // the configuration a launch uses: the installed one, else the default with whole-line tiles where
 // bri_stencil_cfg cannot express them

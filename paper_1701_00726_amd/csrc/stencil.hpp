@@ -75,6 +75,7 @@ struct StencilConfig {
     int rpt;        // multi-RHS kernel: right-hand sides per thread (0 = use the 1-RHS kernel)
     int xcd_remap;  // 1 = give each XCD a contiguous range of tiles
     int lines = 0;    // see below
+    int small = 0;    // see below
     int variant = 0;  // 1-RHS kernel variant (rpt must be 0 for 1 and 2):
                       //   VAR_STANDARD  the 64-site tile kernel above;
                       //   VAR_TSTREAM   t-streaming: xyz tile tile[0..2] (256 sites), chunks of
@@ -89,6 +90,9 @@ struct StencilConfig {
 // StencilConfig::lines > 0 replaces the tile by `lines` whole x-lines (at most 64 sites, lines * L_x, the
 // last tile row along y possibly with fewer) in the columns of colz and coly, for lattices whose
 // x-lines do not fill a wave's 64 lanes evenly; set by default_config only.
+
+// StencilConfig::small = 4 or 8: the small-lattice kernel of stencil_small.hpp with that many waves on
+// every 16 sites; set by default_config only.
 
 enum StencilVariant { VAR_STANDARD = 0, VAR_TSTREAM = 1, VAR_XLINE = 2, VAR_MFMA = 3 };
 

@@ -788,6 +788,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
 }  // namespace bri
 
 #include "stencil_mfma.hpp"
+#include "stencil_small.hpp"
 
 namespace bri {
 
@@ -902,8 +903,30 @@ inline hipError_t launch_mfma(const StencilArgs &a, int mode, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <class LS, int NW, bool DAG> inline hipError_t launch_small(const StencilArgs &a, int mode, hipStream_t st) {
+    using C = typename Cx<typename LS::R>::T;
+    const dim3 grid = group_grid(a, a.ncol, 64 * NW), block(64 * NW);
+    const size_t lds = sizeof(C) * 4 * NW * 12 * SMALL_SITES;
+    switch (mode) {
+    case EPI_PLAIN: hipLaunchKernelGGL((stencil_small_kernel<LS, NW, DAG, EPI_PLAIN>), grid, block, lds, st, a); break;
+    case EPI_NORMS: hipLaunchKernelGGL((stencil_small_kernel<LS, NW, DAG, EPI_NORMS>), grid, block, lds, st, a); break;
+    case EPI_CG_R: hipLaunchKernelGGL((stencil_small_kernel<LS, NW, DAG, EPI_CG_R>), grid, block, lds, st, a); break;
+    case EPI_OV: hipLaunchKernelGGL((stencil_small_kernel<LS, NW, DAG, EPI_OV>), grid, block, lds, st, a); break;
+    case EPI_SIGN: hipLaunchKernelGGL((stencil_small_kernel<LS, NW, DAG, EPI_SIGN>), grid, block, lds, st, a); break;
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 template <class LS, bool DAG, int KIND>
 inline hipError_t launch_cfg(const StencilArgs &a, int mode, const StencilConfig &cfg, hipStream_t st) {
+    if (cfg.small > 0) {
+        if constexpr (KIND == KERN_BRI) {
+            if (cfg.small == 4) return launch_small<LS, 4, DAG>(a, mode, st);
+            if (cfg.small == 8) return launch_small<LS, 8, DAG>(a, mode, st);
+        }
+        return hipErrorInvalidValue;
+    }
     if (cfg.variant == VAR_MFMA) {
         if constexpr (KIND == KERN_BRI && !std::is_same<LS, LinkF64>::value) {
             switch (cfg.rpt) {
@@ -948,7 +971,9 @@ inline hipError_t launch_cfg(const StencilArgs &a, int mode, const StencilConfig
         case 1: return launch_1rhs<LS, 1, DAG, KIND>(a, mode, st);
         case 2: return launch_1rhs<LS, 2, DAG, KIND>(a, mode, st);
         case 4: return launch_1rhs<LS, 4, DAG, KIND>(a, mode, st);
-        case 12: return launch_1rhs<LS, 12, DAG, KIND>(a, mode, st);
+        case 12:
+            if constexpr (KIND == KERN_BRI && std::is_same<LS, LinkF64>::value) return launch_1rhs<LS, 12, DAG, KIND>(a, mode, st);
+            return hipErrorInvalidValue;
         default: return hipErrorInvalidValue;
         }
     case 1: return launch_mrhs<LS, 1, DAG, KIND>(a, mode, st);

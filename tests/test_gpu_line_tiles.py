@@ -1,5 +1,5 @@
 """Launches on tiles of whole x-lines that do not fill a wave's 64 lanes, or a tile row that does not
-divide L_y, and the twelve-wave launch of small lattices: the Brillouin and Wilson operators, their
+divide L_y, the twelve-wave launch and the small-lattice kernel: the Brillouin and Wilson operators, their
 adjoints and the solver epilogues against the oracle (App. C.1 stencil, eq. (def_wils), Sec. 3.3).
 
 Tolerances: the operator is a sum of 81 terms of 3 products with weights summing to about 4, so a
@@ -20,9 +20,10 @@ LATTICES = [
     (20, 7, 8, 16),  # 3 lines a tile (60 lanes), the last tile row holds one
     (33, 4, 8, 16),  # 1 line a tile, 33 lanes
     (24, 12, 6, 12),  # 2 lines a tile (48 lanes), columns of several tile rows and planes
-    (9, 8, 8, 8),  # 7 lines, then 1; twelve waves a tile
-    (64, 3, 4, 4),  # full waves, twelve waves a tile
-    (5, 4, 4, 8),  # 20 of 64 lanes would be used: cut 64-site tiles, twelve waves
+    (9, 8, 8, 8),  # 7 lines, then 1; twelve waves a tile in FP64
+    (64, 3, 4, 4),  # the small-lattice kernel, eight and four waves, and full 64-site lines
+    (5, 4, 4, 8),  # the small-lattice kernel up to all 9 right-hand sides
+    (4, 4, 4, 1),  # extents of one site: a slab's both neighbours coincide
 ]
 
 
@@ -71,7 +72,8 @@ def test_line_tiles_wilson(fields, L):
             assert rel_l2(gotd[r], oracle.dirac_adj(L, K, -0.8, psi[r])) < 1e-14, r
 
 
-@pytest.mark.parametrize("L,nrhs", [((20, 7, 4, 8), 1), ((20, 7, 4, 8), 4), ((9, 8, 8, 8), 1), ((33, 4, 4, 8), 3)])
+@pytest.mark.parametrize("L,nrhs", [((20, 7, 4, 8), 1), ((20, 7, 4, 8), 4), ((9, 8, 8, 8), 1), ((33, 4, 4, 8), 3),
+                                    ((5, 4, 4, 8), 1), ((5, 4, 4, 8), 5)])
 def test_line_tiles_in_the_solver(L, nrhs):
     """The norm and residual epilogues: one pair of partial sums per tile, idle lanes adding nothing."""
     need_gpu()
