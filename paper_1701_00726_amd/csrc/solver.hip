@@ -210,13 +210,10 @@ __global__ void ms_scalar_init_kernel(ColState *states, const double *partial, i
     }
 }
 
-// alpha and the shifted alpha^sigma after t = X p (partials: |t|^2, |p|^2).  Every thread forms
-// alpha from the same sums; thread i < nshift updates shift i, thread 0 the column scalars.
-template <int T>
-__global__ __launch_bounds__(T) void ms_alpha_kernel(ColState *states, const double *partial, int nblk) {
-    ColState *st = states + blockIdx.x;
-    if (st->done) return;
-    const double2 sums = block_sum2<T>(partial + 2 * (size_t)blockIdx.x * nblk, nblk);
+// alpha = |r|^2 / p^H (A + sigma0) p of column st from the sums |t|^2, |p|^2 and the shifted alpha^sigma.
+// Thread i < nshift updates shift i, thread 0 the column scalars; returns whether alpha is usable (the
+// same in every thread; every thread reads st->rr and st->done before).
+__device__ __forceinline__ bool alpha_step(ColState *st, double2 sums) {
     const double pAp = sums.x + st->sigma0 * sums.y;
     const double alpha = st->rr / pAp;
     const bool bad = !isfinite(alpha) || pAp <= 0.0;
@@ -233,13 +230,20 @@ __global__ __launch_bounds__(T) void ms_alpha_kernel(ColState *states, const dou
             st->alpha_s[i] = alpha * zn / z;
         }
     }
-    if (i == 0) {
-        if (bad) {
-            st->status = BRI_ENAN;
-            st->done = 1;
-        } else {
-            st->alpha = alpha;
-        }
+    if (i == 0 && !bad) st->alpha = alpha;
+    return !bad;
+}
+
+// alpha after t = X p (partials: |t|^2, |p|^2) as a launch of its own, where the stencil after it does
+// not form alpha itself
+template <int T>
+__global__ __launch_bounds__(T) void ms_alpha_kernel(ColState *states, const double *partial, int nblk) {
+    ColState *st = states + blockIdx.x;
+    if (st->done) return;
+    const double2 sums = block_sum2<T>(partial + 2 * (size_t)blockIdx.x * nblk, nblk);
+    if (!alpha_step(st, sums) && threadIdx.x == 0) {
+        st->status = BRI_ENAN;
+        st->done = 1;
     }
 }
 
@@ -249,19 +253,38 @@ __global__ __launch_bounds__(T) void ms_alpha_kernel(ColState *states, const dou
 // Stopping: shift i by itself once |r_i| <= tol_i |b|; with the result bound (joint), shift i
 // once ebw_i |r_i| <= tol |b| / (2 nshift), and every shift once sum_i ebw_i |r_i| <= tol |b|
 // (a stopped shift counts with its residual when it stopped).
+// With dots (the stencil formed alpha itself) the alpha step comes first, from the same sums.
 template <int T>
-__global__ __launch_bounds__(T) void ms_beta_kernel(ColState *states, const double *partial, int nblk, WinState *ws, int xmode) {
+__global__ __launch_bounds__(T) void ms_beta_kernel(ColState *states, const double *partial, int nblk,
+                                                    const double *dots, int ndots, WinState *ws, int xmode) {
     ColState *st = states + blockIdx.x;
     if (st->done) {
         if (st->done == 2 && threadIdx.x == 0) st->done = 1;  // its last vector update ran an iteration ago
+        return;
+    }
+    // the window's coefficients of this thread's shift are requested before the sums are formed
+    WinState *w = ws + blockIdx.x;
+    const int i = threadIdx.x;
+    const int ns = st->nshift;
+    const int m = ws ? w->wn : 0;
+    double cw[WIN] = {}, aw = 0.0, ew = 0.0;
+    if (ws && i < ns) {
+        aw = w->a[i];
+        ew = w->e[i];
+#pragma unroll
+        for (int j = 0; j < WIN; ++j) cw[j] = w->c[i][j + 1];  // zero past m
+    }
+    if (dots && !alpha_step(st, block_sum2<T>(dots + 2 * (size_t)blockIdx.x * ndots, ndots))) {
+        if (i == 0) {
+            st->status = BRI_ENAN;
+            st->done = 1;
+        }
         return;
     }
     const double rr_new = block_sum2<T>(partial + 2 * (size_t)blockIdx.x * nblk, nblk).x;
     const bool bad = !isfinite(rr_new);
     const double beta = rr_new / st->rr;
     const int it = st->iter + 1;
-    const int i = threadIdx.x;
-    const int ns = st->nshift;
     int still = 0;
     double res2 = 0.0, term = 0.0;  // |r_i|^2 of a shift still running; its bound term
     if (i < ns) {
@@ -306,40 +329,43 @@ __global__ __launch_bounds__(T) void ms_beta_kernel(ColState *states, const doub
     // (wave 0 holds every shift, so the reads of c precede its writes in program order)
     bool overflow = false;
     if (ws && !bad && i < 64) {
-        WinState *w = ws + blockIdx.x;
-        const int m = w->wn;
         overflow = m >= WIN;  // the host folds every WIN iterations; never reached
         if (!overflow) {
             // y += sum_sigma omega alpha^sigma p^sigma, or x^sigma += alpha^sigma p^sigma (the
             // shifts that took their step)
             const bool step = i < ns && st->upd_x[i];
             const double wgt = step ? (xmode ? 1.0 : st->omega[i]) * st->alpha_s[i] : 0.0;
-            if (i < ns) w->e[i] += wgt * w->a[i];
+            if (i < ns) w->e[i] = ew + wgt * aw;
             if (xmode) {
                 if (step)
-                    for (int j = 1; j <= m; ++j) w->h[i][j] += wgt * w->c[i][j];
+#pragma unroll
+                    for (int j = 0; j < WIN; ++j)
+                        if (j < m) w->h[i][j + 1] += wgt * cw[j];
             } else {
                 // eight sums over the shifts at once: lane i puts its terms in LDS, lane 8 (j - 1) + k
                 // adds those of shifts k, k + 8, ..., and eight lanes meet in three exchanges
                 __shared__ double terms[MAXS][WIN + 1];
-                if (i < ns)
-                    for (int j = 1; j <= m; ++j) terms[i][j] = wgt * w->c[i][j];
-                __builtin_amdgcn_wave_barrier();
                 const int j = (i >> 3) + 1;
+                const double fj = w->f[j];
+                if (i < ns)
+#pragma unroll
+                    for (int l = 0; l < WIN; ++l) terms[i][l] = wgt * cw[l];
+                __builtin_amdgcn_wave_barrier();
                 double v = 0.0;
                 if (j <= m)
-                    for (int k = i & 7; k < ns; k += 8) v += terms[k][j];
+                    for (int k = i & 7; k < ns; k += 8) v += terms[k][j - 1];
 #pragma unroll
                 for (int off = 4; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-                if (j <= m && (i & 7) == 0) w->f[j] += v;
+                if (j <= m && (i & 7) == 0) w->f[j] = fj + v;
             }
             // p^sigma <- zeta_{k+1} r_{k+1} + beta^sigma p^sigma for the shifts still running;
             // the base direction p <- r_{k+1} + beta p always
             if (i < ns && (i == 0 || st->active[i])) {
-                const double bs = i == 0 ? beta : st->beta_s[i];
-                w->a[i] *= bs;
-                for (int j = 1; j <= m; ++j) w->c[i][j] *= bs;
-                w->c[i][m + 1] = i == 0 ? 1.0 : st->zeta[i];
+                const double bs = i == 0 ? beta : st->beta_s[i], z = i == 0 ? 1.0 : st->zeta[i];
+                w->a[i] = bs * aw;
+#pragma unroll
+                for (int j = 0; j < WIN; ++j)
+                    if (j <= m) w->c[i][j + 1] = j == m ? z : bs * cw[j];
             }
             if (i == 0) w->wn = m + 1;
         }
@@ -751,7 +777,7 @@ struct MsSolve {
     int max_iter = 1000;
     // workspace pieces
     ColState *st = nullptr;
-    double *partial = nullptr;
+    double *partial = nullptr, *dots = nullptr;  // partial sums; those of t, read by the next stencil
     int *alldone = nullptr;
     void *r = nullptr, *p = nullptr, *t = nullptr, *y = nullptr, *x = nullptr, *ps = nullptr;
     // deferred shift updates: window state, the base direction at the
@@ -761,11 +787,12 @@ struct MsSolve {
     void *P0 = nullptr, *R = nullptr, *P0_lo = nullptr, *R_lo = nullptr;
 
 
-    void carve(Arena &ar) { carve(ar, stencil_max_slots(g)); }
-    void carve(Arena &ar, int nslots) {
+    void carve(Arena &ar) { carve(ar, stencil_max_slots(g), stencil_max_slots(g)); }
+    void carve(Arena &ar, int nslots, int ndots) {
         const int nb = nslots > INIT_BLOCKS ? nslots : INIT_BLOCKS;
         st = (ColState *)ar.take(sizeof(ColState) * ncol);
         partial = (double *)ar.take(sizeof(double) * 2 * (size_t)nb * ncol);
+        dots = (double *)ar.take(sizeof(double) * 2 * (size_t)(ndots < MAX_DOTS ? ndots : MAX_DOTS) * ncol);
         alldone = (int *)ar.take(sizeof(int));
         const size_t vb = (size_t)12 * g.V * sizeof(double2) * ncol;
         r = ar.take(vb);
@@ -954,6 +981,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         int prec;
         StencilConfig cfg;
         int nslots;  // partial sums per column its stencils leave
+        bool fused;  // the second stencil forms alpha itself
         StencilArgs a1, a2;
         void *r, *p, *ps;
         void *P0, *R;  // deferred updates: base direction at the window's start, stored residuals
@@ -963,6 +991,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         ph.prec = prec;
         ph.cfg = default_config(s.g, prec, s.ncol, s.kind);
         ph.nslots = stencil_slots(s.g, ph.cfg);
+        ph.fused = forms_alpha(ph.cfg, ph.nslots);
         ph.a1 = StencilArgs{};
         ph.a1.g = s.g;
         ph.a1.W = W;
@@ -974,6 +1003,11 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         ph.a1.partial = s.partial;
         ph.a1.st = s.st;
         ph.a2 = ph.a1;
+        if (ph.fused) {
+            ph.a1.partial = s.dots;
+            ph.a2.dots = s.dots;
+            ph.a2.ndots = ph.nslots;
+        }
         ph.a2.in = t;
         ph.a2.out = nullptr;
         ph.a2.p = p;
@@ -995,18 +1029,18 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
     auto iteration = [&](const Phase &ph, bool lo, hipStream_t q) -> int {
         const bool wide = ph.nslots >= RED_WIDE_SLOTS;
         const int e1 = stencil_launch(ph.a1, ph.prec, false, EPI_NORMS, ph.cfg, q);
-        if (wide)
+        if (!ph.fused && wide)
             hipLaunchKernelGGL(ms_alpha_kernel<RED_WIDE>, dim3(s.ncol), dim3(RED_WIDE), 0, q, s.st, s.partial, ph.nslots);
-        else
+        else if (!ph.fused)
             hipLaunchKernelGGL(ms_alpha_kernel<RED_THREADS>, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial,
                                ph.nslots);
         const int e2 = stencil_launch(ph.a2, ph.prec, true, EPI_CG_R, ph.cfg, q);
         if (wide)
             hipLaunchKernelGGL(ms_beta_kernel<RED_WIDE>, dim3(s.ncol), dim3(RED_WIDE), 0, q, s.st, s.partial, ph.nslots,
-                               s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
+                               ph.a2.dots, ph.a2.ndots, s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
         else
             hipLaunchKernelGGL(ms_beta_kernel<RED_THREADS>, dim3(s.ncol), dim3(RED_THREADS), 0, q, s.st, s.partial,
-                               ph.nslots, s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
+                               ph.nslots, ph.a2.dots, ph.a2.ndots, s.windowed ? s.ws : nullptr, s.store_x ? 1 : 0);
         if (s.windowed && !lo)
             hipLaunchKernelGGL((ms_pupdate_kernel<double2>), ugrid, dim3(256), 0, q, s.st, s.ws, n, s.ncol,
                                (const double2 *)ph.r, (double2 *)ph.p, (double2 *)ph.R);
@@ -1075,7 +1109,7 @@ static int ms_run(MsSolve &s, const void *b, hipStream_t strm, int *hflag, RunSt
         std::memcpy(&swbits, &sw2, sizeof(swbits));
         key0 = {(uint64_t)dev, (uint64_t)s.g.L[0], (uint64_t)s.g.L[1], (uint64_t)s.g.L[2], (uint64_t)s.g.L[3],
                 (uint64_t)s.g.tbc, cswbits, (uint64_t)s.prec, (uint64_t)s.kind, (uint64_t)s.ncol, m0bits,
-                (uint64_t)(uintptr_t)s.W, (uint64_t)(uintptr_t)s.st, (uint64_t)(uintptr_t)s.partial,
+                (uint64_t)(uintptr_t)s.W, (uint64_t)(uintptr_t)s.st, (uint64_t)(uintptr_t)s.partial, (uint64_t)(uintptr_t)s.dots,
                 (uint64_t)(uintptr_t)s.alldone, (uint64_t)(uintptr_t)s.r, (uint64_t)(uintptr_t)s.p,
                 (uint64_t)(uintptr_t)s.t, (uint64_t)(uintptr_t)s.y, (uint64_t)(uintptr_t)s.x,
                 (uint64_t)(uintptr_t)s.ps, (uint64_t)(int64_t)s.prec_lo, (uint64_t)(uintptr_t)s.Wlo,
@@ -1273,8 +1307,8 @@ static void fill_stats(const RunStats &rs, int n, ov_stats *st) {
 // held until the process ends, resolved once per device with hipGetSymbolAddress (the array's
 // name is only a host-side stand-in).  Every call on a GPU shares it.
 // Whether a problem fits is decided with one pair of partial sums per 64 sites; the array is larger by
-// what the launches with smaller tiles may leave (16 bytes per 64 sites and column more, and a problem
-// that fits has at most 256 MiB / (4 vectors of 192 bytes) = 350000 sites and columns).
+// what the launches with smaller tiles may leave (one pair of 16 bytes per 16 sites and column, twice,
+// and a problem that fits has at most 256 MiB / (4 vectors of 192 bytes) = 350000 sites and columns).
 constexpr size_t SCRATCH_BYTES = (size_t)256 << 20, SCRATCH_SLACK = (size_t)1 << 20;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + SCRATCH_SLACK];
 constexpr int SCRATCH_MAX_DEVICES = 64;
@@ -1316,7 +1350,7 @@ static int ov_impl(const bri_geom *geom, const void *W64, const void *Wlo, const
     size_t scratch_bytes = 0;
     if (noalloc) {
         Arena ar(nullptr);
-        m.carve(ar, g.V / 64);
+        m.carve(ar, g.V / 64, 0);
         if (ar.used > SCRATCH_BYTES) return BRI_ESCRATCH;
         rc = scratch_address(&work);
         if (rc != BRI_OK) return rc;

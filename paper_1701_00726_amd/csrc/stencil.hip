@@ -256,6 +256,11 @@ static void line_columns(const Geom &g, int lines, int cap, StencilConfig &c) {
         }
 }
 
+bool forms_alpha(const StencilConfig &cfg, int ndots) {
+    if (cfg.variant == VAR_TSTREAM || cfg.variant == VAR_MFMA) return false;
+    return ndots <= MAX_DOTS && (cfg.small > 0 || cfg.rpt == 0);
+}
+
 // Replaces the tile configuration by the small-lattice kernel or whole-line tiles where they measured
 // faster.
 static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilConfig &c) {

@@ -60,6 +60,8 @@ struct StencilArgs {
     const void *p;          // EPI_CG_R
     void *r;                // EPI_CG_R
     const ColState *st;     // EPI_NORMS / EPI_CG_R: alpha, sigma0 and the done flag per column
+    const double *dots;     // EPI_CG_R: [ncol][ndots][2], the partial sums |t|^2, |p|^2 from which each
+    int ndots;              // block forms alpha by itself; NULL: alpha is in st
     const void *b;          // EPI_OV / EPI_RESID
     int b_mod;              // EPI_RESID: column c uses b column (c % b_mod)
     const void *xs;         // EPI_RESID
@@ -110,6 +112,10 @@ StencilConfig untuned_config(const Geom &g, int prec, int ncol, int kind);
 StencilConfig tile_config(const Geom &g, int prec, int ncol, int kind);
 int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilConfig &cfg, hipStream_t st);
 
+// whether the EPI_CG_R launch of cfg forms alpha itself from ndots partial sums per column (the kernels
+// with one column per block)
+constexpr int MAX_DOTS = 2048;
+bool forms_alpha(const StencilConfig &cfg, int ndots);
 // partial-sum slots per column a launch with cfg fills, and the most any configuration fills
 int stencil_slots(const Geom &g, const StencilConfig &cfg);
 int stencil_max_slots(const Geom &g);

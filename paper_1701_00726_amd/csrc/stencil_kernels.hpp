@@ -53,7 +53,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // contributions (n0, n1) where the mode has any.
 template <int MODE, typename C, typename R>
 __device__ __forceinline__ void epilogue(const StencilArgs &a, int col, int comp, unsigned x, unsigned V, C v,
-                                         double &n0, double &n1) {
+                                         double &n0, double &n1, double alpha = 0.0) {
     const size_t idx = ((size_t)col * 12 + comp) * V + x;
     if constexpr (MODE == EPI_PLAIN) {
         ((C *)a.out)[idx] = v;
@@ -65,7 +65,7 @@ __device__ __forceinline__ void epilogue(const StencilArgs &a, int col, int comp
         const C pp = ((const C *)a.p)[idx];
         C *rr = (C *)a.r;
         C r = rr[idx];
-        const R al = (R)a.st[col].alpha;
+        const R al = (R)alpha;
         const R s0 = (R)a.st[col].sigma0;
         const R apx = v.x + s0 * pp.x, apy = v.y + s0 * pp.y;
         r.x = fma(-al, apx, r.x);
@@ -88,6 +88,48 @@ __device__ __forceinline__ void epilogue(const StencilArgs &a, int col, int comp
         ((C *)a.out)[idx] = o;
         n0 += norm2(o);
     }
+}
+
+// alpha of column col for EPI_CG_R: from the state, or formed by the block from the partial sums of the
+// launch before it (a.dots; called by every thread of the block, when its main loop is done: the sums
+// come from L2, and no register is held for them meanwhile)
+template <int MODE> __device__ __forceinline__ double block_alpha(const StencilArgs &a, int col) {
+    if constexpr (MODE == EPI_CG_R) {
+        if (!a.dots) return a.st[col].alpha;
+        __shared__ double2 sums[16];
+        const double2 *p = (const double2 *)a.dots + (size_t)col * a.ndots;
+        double sx = 0.0, sy = 0.0;
+        for (int i = threadIdx.x; i < a.ndots; i += 4 * blockDim.x) {
+            double2 v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int ik = i + k * (int)blockDim.x;
+                v[k] = p[ik < a.ndots ? ik : i];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const bool in = i + k * (int)blockDim.x < a.ndots;
+                sx += in ? v[k].x : 0.0;
+                sy += in ? v[k].y : 0.0;
+            }
+        }
+        sx = wave_sum(sx);
+        sy = wave_sum(sy);
+        if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = make_double2(sx, sy);
+        __syncthreads();
+        sx = sy = 0.0;
+        for (int w = 0; w < (int)blockDim.x / 64; ++w) {
+            sx += sums[w].x;
+            sy += sums[w].y;
+        }
+        return a.st[col].rr / (sx + a.st[col].sigma0 * sy);
+    }
+    return 0.0;
+}
+
+template <int MODE> __device__ __forceinline__ double col_alpha(const StencilArgs &a, int col) {
+    if constexpr (MODE == EPI_CG_R) return a.st[col].alpha;
+    return 0.0;
 }
 
 template <int MODE> __device__ __forceinline__ bool col_done(const StencilArgs &a, int col) {
@@ -186,6 +228,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     // combine the NSPLIT partial sums through LDS
     __shared__ double wsum[NSPLIT][2];
     C res[NCOMP];
+    const double alpha = block_alpha<MODE>(a, col);
     combine<NSPLIT>(res, acc, q, lane);
     if (q >= NFIN) site = false;  // (waves beyond the first four hold no component)
 
@@ -196,7 +239,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     double n0 = 0.0, n1 = 0.0;
 #pragma unroll
     for (int i = 0; i < NCOMP; ++i)
-        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
+        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1, alpha);
     if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
         // deterministic: wave sums, then the NSPLIT wave totals in order
         n0 = wave_sum(n0);
@@ -332,6 +375,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
 
     __shared__ double wsum[NSPLIT][2];
     C res[NCOMP];
+    const double alpha = block_alpha<MODE>(a, col);
     combine<NSPLIT>(res, acc, q, lane);
     if (q >= NFIN) site = false;  // (waves beyond the first four hold no component)
     if (a.g.csw != 0.0 && q < NFIN) {
@@ -341,7 +385,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
     double n0 = 0.0, n1 = 0.0;
 #pragma unroll
     for (int i = 0; i < NCOMP; ++i)
-        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1);
+        if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1, alpha);
     if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
         n0 = wave_sum(n0);
         n1 = wave_sum(n1);
@@ -474,7 +518,7 @@ __global__ __launch_bounds__(64 * MRHS_SPLIT) void stencil_xline_mrhs_kernel(Ste
             }
             if (a.g.csw != 0.0)
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
-            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
+            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1, col_alpha<MODE>(a, col));
         }
         if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
             n0 = wave_sum(n0);
@@ -600,7 +644,7 @@ __global__ __launch_bounds__(STREAM_THREADS) void stencil_stream_kernel(StencilA
                 for (int b = 0; b < 3; ++b) {
                     C v = accp[sp][b];
                     if (a.g.csw != 0.0) clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in, sp * 3 + b, x, V);
-                    epilogue<MODE, C, R>(a, col, sp * 3 + b, x, V, v, n0, n1);
+                    epilogue<MODE, C, R>(a, col, sp * 3 + b, x, V, v, n0, n1, col_alpha<MODE>(a, col));
                 }
         }
         if (last) break;
@@ -759,7 +803,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
             }
             if (a.g.csw != 0.0)
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
-            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1);
+            if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1, col_alpha<MODE>(a, col));
         }
         if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
             // deterministic: wave sums, then the NSPLIT wave totals in order

@@ -115,6 +115,7 @@ __global__ __launch_bounds__(64 * NW) void stencil_small_kernel(StencilArgs a) {
     for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int b = 0; b < 3; ++b) red[grp][s * 3 + b][l] = acc[s][b];
+    const double alpha = block_alpha<MODE>(a, col);
     __syncthreads();
 
     double n0 = 0.0, n1 = 0.0;
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(64 * NW) void stencil_small_kernel(StencilArgs a) {
             v.y += u.y;
         }
         if (a.g.csw != 0.0) clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in, comp, x, V);
-        epilogue<MODE, C, R>(a, col, comp, x, V, v, n0, n1);
+        epilogue<MODE, C, R>(a, col, comp, x, V, v, n0, n1, alpha);
     }
     if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
         // the twelve components sit in the first three waves; wave sums, then their totals in order

@@ -87,3 +87,17 @@ def test_line_tiles_in_the_solver(L, nrhs):
     for r in range(nrhs):
         ref, _, _ = oracle.ov_apply(L, Wo, 1.0, 6, b[r], tol=1e-13)
         assert rel_l2(got[r], ref) < 1e-10, r
+
+
+@pytest.mark.parametrize("L", [(32, 8, 8, 64), (16, 16, 16, 34), (12, 12, 12, 12)])
+def test_alpha_formed_by_the_stencil(L):
+    """Up to 2048 partial sums the residual stencil of a single column forms alpha itself; four columns on the
+    kernels with several columns per thread take it from a launch of its own.  Both stop at the same bound."""
+    need_gpu()
+    U = synth.smeared_links(L, 0.5, 5500, 0.6, 1)
+    W = bri.build_links(L, bri.links_to_device(U), bri.F64)
+    b = bri.spinor_to_device(synth.gaussian_source(L, 5501, nrhs=4))
+    print(f"[lines] alpha {L}", flush=True)
+    four, _ = bri.OverlapOp(L, W, kl_n=4, tol=1e-12, nrhs=4).apply(b)
+    one, _ = bri.OverlapOp(L, W, kl_n=4, tol=1e-12, nrhs=1).apply(b[2:3].contiguous())
+    assert rel_l2(bri.spinor_to_host(one)[0], bri.spinor_to_host(four)[2]) < 1e-10
