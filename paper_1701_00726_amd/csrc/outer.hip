@@ -16,9 +16,16 @@
 //
 // Several right-hand sides run side by side, each with its own BiCGstab scalars; every operator
 // application treats all of them in one batched call.  A column that has converged keeps its x
-// and r (its coefficients become those of the identity) until every column is done.  The host
-// drives the recurrences; every vector operation and reduction runs on the device, reductions in
-// FP64 with fixed block partial sums added in order on the host (deterministic).
+// and r until every column is done.  The host drives the recurrences; every vector operation and
+// reduction runs on the device, reductions in FP64 with fixed block partial sums added in order on
+// the host (deterministic).
+//
+// A half step of the kernel level is a stencil of 45 to 70 us (12^3 x 24, two columns, FP32) and vector
+// work that a launch each would make as long, so what belongs together is one launch: a combination
+// with the copy the stencil reads, or with the stencil's result and the dot products of the outcome
+// (outer_step_kernel), and both updates of an iteration's end with theirs (outer_xr_kernel): five vector
+// launches an iteration instead of sixteen.  The blocks write their partial sums straight into pinned
+// host memory, so a dot product costs no copy, only the wait.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -35,67 +42,14 @@ int geom_check(const bri_geom *geom, Geom *g);
 using cplx = std::complex<double>;
 
 constexpr int MAXC = BRI_MAX_SOLVE_RHS;
-constexpr int DOT_BLOCKS = 256;  // per column
-constexpr int DOT_THREADS = 256;
-
-// partial sums of up to three complex dot products <a_k, b_k> = sum conj(a_k) b_k per column
-// (column = blockIdx.y, vectors [ncol][n]); partial[k][col][block][2]
-__global__ __launch_bounds__(DOT_THREADS) void outer_dots_kernel(size_t n, int nd, const double2 *__restrict__ a0,
-                                                                 const double2 *__restrict__ b0,
-                                                                 const double2 *__restrict__ a1,
-                                                                 const double2 *__restrict__ b1,
-                                                                 const double2 *__restrict__ a2,
-                                                                 const double2 *__restrict__ b2,
-                                                                 double *__restrict__ partial) {
-    const size_t off = (size_t)blockIdx.y * n;
-    double acc[3][2] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-    const double2 *as[3] = {a0, a1, a2};
-    const double2 *bs[3] = {b0, b1, b2};
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        for (int k = 0; k < nd; ++k) {
-            const double2 u = as[k][off + i], v = bs[k][off + i];
-            acc[k][0] += u.x * v.x + u.y * v.y;
-            acc[k][1] += u.x * v.y - u.y * v.x;
-        }
-    }
-    __shared__ double sh[DOT_THREADS];
-    for (int k = 0; k < nd; ++k)
-        for (int c = 0; c < 2; ++c) {
-            sh[threadIdx.x] = acc[k][c];
-            __syncthreads();
-            for (int w = DOT_THREADS / 2; w > 0; w >>= 1) {
-                if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-                __syncthreads();
-            }
-            if (threadIdx.x == 0)
-                partial[(((size_t)k * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 2 + c] = sh[0];
-            __syncthreads();
-        }
-}
+constexpr int STEP_BLOCKS = 512;  // per column, at most
+constexpr int STEP_THREADS = 256;
+constexpr int MAXD = 2;  // dot products per launch
 
 // per-column coefficients of a three-term combination
 struct Coef3 {
     double2 c[MAXC][3];
 };
-
-// out = c0 x0 + c1 x1 + c2 x2 per column (column = blockIdx.y, vectors [ncol][n]); a null vector is
-// a zero term; out may be one of the inputs (elementwise)
-__global__ void outer_lincomb_kernel(size_t n, double2 *out, Coef3 cf, const double2 *x0, const double2 *x1,
-                                     const double2 *x2) {
-    const int col = blockIdx.y;
-    const size_t off = (size_t)col * n;
-    const double2 *xs[3] = {x0, x1, x2};
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        double2 v = make_double2(0.0, 0.0);
-        for (int k = 0; k < 3; ++k) {
-            if (!xs[k]) continue;
-            const double2 u = xs[k][off + i], c = cf.c[col][k];
-            v.x += c.x * u.x - c.y * u.y;
-            v.y += c.x * u.y + c.y * u.x;
-        }
-        out[off + i] = v;
-    }
-}
 
 // Column maps of the kernel level: only the columns still iterating go through its stencil.
 struct ColMap {
@@ -106,24 +60,125 @@ template <typename T> __device__ __forceinline__ T conv(double2 v);
 template <> __device__ __forceinline__ double2 conv<double2>(double2 v) { return v; }
 template <> __device__ __forceinline__ float2 conv<float2>(double2 v) { return make_float2((float)v.x, (float)v.y); }
 
-// out column k = in column map.idx[k] (k = blockIdx.y), converted to T (complex float narrows)
-template <typename T>
-__global__ void outer_gather_kernel(size_t n, ColMap map, const double2 *__restrict__ in, T *__restrict__ out) {
-    const double2 *src = in + (size_t)map.idx[blockIdx.y] * n;
-    T *dst = out + (size_t)blockIdx.y * n;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = conv<T>(src[i]);
+// The block's sums of ND complex numbers per thread, to partial[d][col][block]
+template <int ND>
+__device__ __forceinline__ void step_sums(const double (&acc)[ND > 0 ? ND : 1][2], double2 *partial) {
+    if constexpr (ND > 0) {
+        __shared__ double2 sh[ND][STEP_THREADS / 64];
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            double sx = acc[d][0], sy = acc[d][1];
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                sx += __shfl_down(sx, off, 64);
+                sy += __shfl_down(sy, off, 64);
+            }
+            if (threadIdx.x % 64 == 0) sh[d][threadIdx.x / 64] = make_double2(sx, sy);
+        }
+        __syncthreads();
+        if (threadIdx.x < ND) {
+            double2 t = sh[threadIdx.x][0];
+            for (int w = 1; w < STEP_THREADS / 64; ++w) {
+                t.x += sh[threadIdx.x][w].x;
+                t.y += sh[threadIdx.x][w].y;
+            }
+            partial[((size_t)threadIdx.x * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = t;
+        }
+    }
 }
 
-// out column c = scale * in column inv.idx[c], or zero where inv.idx[c] < 0 (c = blockIdx.y)
-template <typename T>
-__global__ void outer_scatter_kernel(size_t n, ColMap inv, double scale, const T *__restrict__ in,
-                                     double2 *__restrict__ out) {
-    const int k = inv.idx[blockIdx.y];
-    double2 *dst = out + (size_t)blockIdx.y * n;
-    const T *src = in + (size_t)(k < 0 ? 0 : k) * n;
-    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        dst[i] = k < 0 ? make_double2(0.0, 0.0) : make_double2(scale * (double)src[i].x, scale * (double)src[i].y);
+// <u, v> += conj(u) v
+__device__ __forceinline__ void dot_add(double (&acc)[2], double2 u, double2 v) {
+    acc[0] += u.x * v.x + u.y * v.y;
+    acc[1] += u.x * v.y - u.y * v.x;
+}
+
+// One launch of vector work (column = blockIdx.y, vectors [ncol][n]; a null vector is a zero term, out
+// may be one of the inputs, elementwise):
+//   out = c0 x0 + c1 x1 + c2 x2 + kscale K,  K column kmap[col] of the compacted stencil result k
+//         (type T; nothing where kmap < 0),
+//   zero = 0,
+//   column lmap[col] of lo = out converted to T (nothing where lmap < 0),
+//   partial sums of <da, db> for ND pairs, a null vector standing for out.
+struct Step {
+    size_t n;
+    double2 *out, *zero;
+    Coef3 cf;
+    const double2 *x[3];
+    const void *k;
+    double kscale;
+    ColMap kmap;
+    void *lo;
+    ColMap lmap;
+    const double2 *da[MAXD], *db[MAXD];
+    double2 *partial;
+};
+
+template <typename T, int ND>
+__global__ __launch_bounds__(STEP_THREADS) void outer_step_kernel(Step a) {
+    const int col = blockIdx.y;
+    const size_t off = (size_t)col * a.n;
+    const int kc = a.k ? a.kmap.idx[col] : -1, lc = a.lo ? a.lmap.idx[col] : -1;
+    const T *k = (const T *)a.k + (kc < 0 ? 0 : kc) * a.n;
+    T *lo = (T *)a.lo + (lc < 0 ? 0 : lc) * a.n;
+    double acc[ND > 0 ? ND : 1][2] = {};
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < a.n; i += (size_t)gridDim.x * blockDim.x) {
+        double2 u[3], ud[ND > 0 ? ND : 1][2];
+        T uk{};
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (a.x[j]) u[j] = a.x[j][off + i];
+        if (kc >= 0) uk = k[i];
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            if (a.da[d]) ud[d][0] = a.da[d][off + i];
+            if (a.db[d]) ud[d][1] = a.db[d][off + i];
+        }
+        double2 v = make_double2(0.0, 0.0);
+        if (kc >= 0) v = make_double2(a.kscale * (double)uk.x, a.kscale * (double)uk.y);
+#pragma unroll
+        for (int j = 0; j < 3; ++j)
+            if (a.x[j]) {
+                const double2 c = a.cf.c[col][j];
+                v.x += c.x * u[j].x - c.y * u[j].y;
+                v.y += c.x * u[j].y + c.y * u[j].x;
+            }
+        a.out[off + i] = v;
+        if (a.zero) a.zero[off + i] = make_double2(0.0, 0.0);
+        if (lc >= 0) lo[i] = conv<T>(v);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) dot_add(acc[d], a.da[d] ? ud[d][0] : v, a.db[d] ? ud[d][1] : v);
+    }
+    step_sums<ND>(acc, a.partial);
+}
+
+// the end of an iteration, for the columns with c[col][2].x != 0 (the others keep x and r):
+//   x += c0 ph + c1 sh,  r = s - c1 t,  partial sums of <r, r> and <r0, r>
+__global__ __launch_bounds__(STEP_THREADS) void outer_xr_kernel(size_t n, Coef3 cf, double2 *x, double2 *r,
+                                                                const double2 *ph, const double2 *sh,
+                                                                const double2 *s, const double2 *t,
+                                                                const double2 *r0, double2 *partial) {
+    const int col = blockIdx.y;
+    if (cf.c[col][2].x == 0.0) return;
+    const size_t off = (size_t)col * n;
+    const double2 c0 = cf.c[col][0], c1 = cf.c[col][1];
+    double acc[2][2] = {};
+    for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        double2 xv = x[off + i];
+        const double2 p = ph[off + i], q = sh[off + i], sv = s[off + i], tv = t[off + i], z = r0[off + i];
+        xv.x += c0.x * p.x - c0.y * p.y;
+        xv.y += c0.x * p.y + c0.y * p.x;
+        xv.x += c1.x * q.x - c1.y * q.y;
+        xv.y += c1.x * q.y + c1.y * q.x;
+        x[off + i] = xv;
+        double2 rv = sv;
+        rv.x -= c1.x * tv.x - c1.y * tv.y;
+        rv.y -= c1.x * tv.y + c1.y * tv.x;
+        r[off + i] = rv;
+        dot_add(acc[0], rv, rv);
+        dot_add(acc[1], z, rv);
+    }
+    step_sums<2>(acc, partial);
 }
 
 static inline size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -137,10 +192,25 @@ struct Level {
     double tol;
     int max_iter;
     int kprec;  // kernel level: precision of its stencil (BRI_F64, or BRI_F32 / BRI_F32_BF16W on Wlo)
-    double2 *r, *r0, *p, *v, *s, *t, *ph, *sh;  // [ncol][12 V] each
+    double2 *r, *p, *v, *s, *t, *ph, *sh;  // [ncol][12 V] each
     int iters = 0, calls = 0, applies = 0;
 };
-constexpr int NVEC = 8;
+constexpr int NVEC = 7;
+
+// the pinned host memory that the partial sums of one solve go to
+struct HostSums {
+    double2 *p = nullptr;
+    hipStream_t s = nullptr;
+    bool get(size_t count, hipStream_t stream) {
+        s = stream;
+        return hipHostMalloc((void **)&p, count * sizeof(double2), hipHostMallocDefault) == hipSuccess;
+    }
+    ~HostSums() {
+        if (!p) return;
+        (void)hipStreamSynchronize(s);  // a launch of a solve that failed may still write
+        (void)hipHostFree(p);
+    }
+};
 
 struct Cascade {
     const bri_geom *geom;
@@ -154,90 +224,133 @@ struct Cascade {
     size_t ov_bytes;
     float2 *lo_in = nullptr, *lo_out = nullptr;  // low-precision kernel level: [ncol][12 V] each
     double2 *k_in = nullptr, *k_out = nullptr;   // FP64 kernel level, compacted columns
-    double *partial;
-    std::vector<double> hp;
+    HostSums sums;
     std::vector<Level> lev;
     int inner_iters = 0;
     ov_stats ist;
 
     Cols all(cplx v) const { return Cols(ncol, v); }
 
-    int lincomb(double2 *dst, const Cols &c0, const double2 *x0, const Cols &c1 = Cols(), const double2 *x1 = nullptr,
-                const Cols &c2 = Cols(), const double2 *x2 = nullptr) {
-        Coef3 cf{};
+    int blocks() const { return (int)std::min<size_t>(STEP_BLOCKS, (n + STEP_THREADS - 1) / STEP_THREADS); }
+
+    // out = c0 x0 + c1 x1 + c2 x2
+    Step comb(double2 *out, const Cols &c0, const double2 *x0, const Cols &c1 = Cols(), const double2 *x1 = nullptr,
+              const Cols &c2 = Cols(), const double2 *x2 = nullptr) const {
+        Step a{};
+        a.n = n;
+        a.out = out;
         for (int c = 0; c < ncol; ++c) {
             const cplx k[3] = {c0.empty() ? 0.0 : c0[c], c1.empty() ? 0.0 : c1[c], c2.empty() ? 0.0 : c2[c]};
-            for (int j = 0; j < 3; ++j) cf.c[c][j] = make_double2(k[j].real(), k[j].imag());
+            for (int j = 0; j < 3; ++j) a.cf.c[c][j] = make_double2(k[j].real(), k[j].imag());
         }
-        hipLaunchKernelGGL(outer_lincomb_kernel, dim3(1024, ncol), dim3(256), 0, s, n, dst, cf, x0, x1, x2);
+        a.x[0] = x0;
+        a.x[1] = x1;
+        a.x[2] = x2;
+        a.partial = sums.p;
+        return a;
+    }
+
+    // the launch of a, with the compacted vectors k and lo complex float (narrow) or double
+    int run(const Step &a, int nd = 0, bool narrow = false) {
+        const dim3 grid(blocks(), ncol), block(STEP_THREADS);
+        if (nd == 0 && narrow)
+            hipLaunchKernelGGL((outer_step_kernel<float2, 0>), grid, block, 0, s, a);
+        else if (nd == 0)
+            hipLaunchKernelGGL((outer_step_kernel<double2, 0>), grid, block, 0, s, a);
+        else if (nd == 1 && narrow)
+            hipLaunchKernelGGL((outer_step_kernel<float2, 1>), grid, block, 0, s, a);
+        else if (nd == 1)
+            hipLaunchKernelGGL((outer_step_kernel<double2, 1>), grid, block, 0, s, a);
+        else if (nd == 2 && narrow)
+            hipLaunchKernelGGL((outer_step_kernel<float2, 2>), grid, block, 0, s, a);
+        else
+            hipLaunchKernelGGL((outer_step_kernel<double2, 2>), grid, block, 0, s, a);
         return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
     }
 
-    // up to three dot products per column, summed on the host in a fixed order; res[k][col];
-    // synchronises the stream
-    int dots(int nd, const double2 *a0, const double2 *b0, const double2 *a1, const double2 *b1, const double2 *a2,
-             const double2 *b2, std::vector<Cols> &res) {
-        hipLaunchKernelGGL(outer_dots_kernel, dim3(DOT_BLOCKS, ncol), dim3(DOT_THREADS), 0, s, n, nd, a0, b0, a1,
-                           b1, a2, b2, partial);
-        if (hipGetLastError() != hipSuccess) return BRI_EHIP;
-        const size_t cnt = (size_t)2 * nd * ncol * DOT_BLOCKS;
-        if (hipMemcpyAsync(hp.data(), partial, sizeof(double) * cnt, hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return BRI_EHIP;
+    // the nd dot products per column of the launch before, their partial sums added in order;
+    // res[d][col]; synchronises the stream.  Columns outside `act` hold nothing of use.
+    int take_dots(int nd, std::vector<Cols> &res) {
+        if (hipStreamSynchronize(s) != hipSuccess) return BRI_EHIP;
+        const int nb = blocks();
         res.assign(nd, Cols(ncol));
-        for (int k = 0; k < nd; ++k)
+        for (int d = 0; d < nd; ++d)
             for (int c = 0; c < ncol; ++c) {
                 double re = 0.0, im = 0.0;
-                const double *q = hp.data() + ((size_t)k * ncol + c) * DOT_BLOCKS * 2;
-                for (int i = 0; i < DOT_BLOCKS; ++i) {
-                    re += q[2 * i];
-                    im += q[2 * i + 1];
+                const double2 *q = sums.p + ((size_t)d * ncol + c) * nb;
+                for (int i = 0; i < nb; ++i) {
+                    re += q[i].x;
+                    im += q[i].y;
                 }
-                res[k][c] = cplx(re, im);
+                res[d][c] = cplx(re, im);
             }
         return BRI_OK;
     }
+    int run_dots(const Step &a, int nd, std::vector<Cols> &res, bool narrow = false) {
+        const int rc = run(a, nd, narrow);
+        return rc != BRI_OK ? rc : take_dots(nd, res);
+    }
 
-    // dst = D_ov^(n_k) v (kl_n > 0) or rho D_kernel(-rho) v (kl_n = 0); dst != v.  Columns outside
-    // `act` are zero in v and come out zero: the multi-shift drops zero columns at its start, and
-    // the kernel level applies its stencil to the active columns only (gathered, in the level's
-    // precision, and scattered back).
-    int apply_d(Level &L, const double2 *v, double2 *dst, const std::vector<char> &act) {
-        ++L.applies;
-        if (L.kl_n == 0) {
-            const bool wil = L.prm.kernel == BRI_KERNEL_WILSON;
-            ColMap map{}, inv{};
-            int k = 0;
-            for (int c = 0; c < ncol; ++c) {
-                inv.idx[c] = act[c] ? k : -1;
-                if (act[c]) map.idx[k++] = c;
-            }
-            if (k == 0) return lincomb(dst, all(0.0), nullptr);
+    // whether the kernel level's stencil works on a compacted copy of its input: in low precision, or
+    // of the active columns where some are not
+    bool compacted(const Level &L, const std::vector<char> &act) const {
+        return L.kl_n == 0 && (L.kprec != BRI_F64 || std::count(act.begin(), act.end(), 0) > 0);
+    }
+    ColMap compact_map(const std::vector<char> &act, int *k) const {
+        ColMap m{};
+        *k = 0;
+        for (int c = 0; c < ncol; ++c) m.idx[c] = act[c] ? (*k)++ : -1;
+        return m;
+    }
+    // a leaves the copy the stencil of level L reads as well
+    bool feed(Step &a, const Level &L, const std::vector<char> &act) const {
+        if (!compacted(L, act)) return false;
+        int k;
+        a.lmap = compact_map(act, &k);
+        a.lo = L.kprec != BRI_F64 ? (void *)lo_in : (void *)k_in;
+        return L.kprec != BRI_F64;
+    }
+
+    // out = A_k v (a.out, with a's dot products; a holds nothing else yet), out != v.  Columns outside
+    // `act` are zero in v and come out zero: the multi-shift drops zero columns at its start, and the
+    // kernel level applies its stencil to the active columns only, from the copy that the launch which
+    // made v left (feed), in the level's precision.
+    int apply_a(Level &L, const double2 *v, Step a, const std::vector<char> &act, int nd, std::vector<Cols> &res) {
+        double2 *dst = a.out;
+        const Step dotted = a;
+        if (L.kl_n == 0 && compacted(L, act)) {
+            ++L.applies;
             const bool lo = L.kprec != BRI_F64;
-            if (!lo && k == ncol) {  // every column active: no compaction
-                const int r = wil ? ::wil_apply(geom, W64, BRI_F64, -rho, v, dst, ncol, s)
-                                  : ::bri_apply(geom, W64, BRI_F64, -rho, v, dst, ncol, s);
-                if (r != BRI_OK) return r;
-                return lincomb(dst, all(rho), dst);
-            }
-            if (lo)
-                hipLaunchKernelGGL(outer_gather_kernel<float2>, dim3(1024, k), dim3(256), 0, s, n, map, v, lo_in);
-            else
-                hipLaunchKernelGGL(outer_gather_kernel<double2>, dim3(1024, k), dim3(256), 0, s, n, map, v, k_in);
-            const void *Wk = lo ? Wlo : W64;
-            const void *in_k = lo ? (const void *)lo_in : (const void *)k_in;
-            void *out_k = lo ? (void *)lo_out : (void *)k_out;
-            const int r = wil ? ::wil_apply(geom, Wk, L.kprec, -rho, in_k, out_k, k, s)
-                              : ::bri_apply(geom, Wk, L.kprec, -rho, in_k, out_k, k, s);
+            int k;
+            a = comb(dst, all(rho + mt), v);
+            a.kmap = compact_map(act, &k);
+            a.k = lo ? (const void *)lo_out : (const void *)k_out;
+            a.kscale = rho;
+            const int r = kernel_apply(L, lo ? Wlo : W64, lo ? (const void *)lo_in : (const void *)k_in,
+                                       lo ? (void *)lo_out : (void *)k_out, k);
             if (r != BRI_OK) return r;
-            if (lo)
-                hipLaunchKernelGGL(outer_scatter_kernel<float2>, dim3(1024, ncol), dim3(256), 0, s, n, inv, rho,
-                                   lo_out, dst);
-            else
-                hipLaunchKernelGGL(outer_scatter_kernel<double2>, dim3(1024, ncol), dim3(256), 0, s, n, inv, rho,
-                                   k_out, dst);
-            return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
+        } else {
+            const int r = apply_d(L, v, dst);
+            if (r != BRI_OK) return r;
+            a = L.kl_n == 0 ? comb(dst, all(rho), dst, all(rho + mt), v) : comb(dst, all(1.0), dst, all(mt), v);
         }
+        for (int d = 0; d < MAXD; ++d) {
+            a.da[d] = dotted.da[d];
+            a.db[d] = dotted.db[d];
+        }
+        return run_dots(a, nd, res, L.kl_n == 0 && L.kprec != BRI_F64);
+    }
+
+    // D_kernel(-rho) of k columns in the level's precision
+    int kernel_apply(const Level &L, const void *W, const void *in, void *out, int k) {
+        return L.prm.kernel == BRI_KERNEL_WILSON ? ::wil_apply(geom, W, L.kprec, -rho, in, out, k, s)
+                                                 : ::bri_apply(geom, W, L.kprec, -rho, in, out, k, s);
+    }
+
+    // dst = D_ov^(n_k) v (kl_n > 0) or D_kernel(-rho) v (kl_n = 0) of every column; dst != v
+    int apply_d(Level &L, const double2 *v, double2 *dst) {
+        ++L.applies;
+        if (L.kl_n == 0) return kernel_apply(L, W64, v, dst, ncol);
         size_t ob = ov_bytes;
         const int r = ::ov_apply(geom, W64, Wlo, &L.prm, v, dst, ncol, ov, &ob, &ist, s);
         inner_iters += ist.iters;
@@ -245,16 +358,11 @@ struct Cascade {
         return (r == BRI_ENOCONV && &L != &lev[0]) ? BRI_OK : r;
     }
 
-    // dst = A_k v
-    int apply_a(Level &L, const double2 *v, double2 *dst, const std::vector<char> &act) {
-        const int r = apply_d(L, v, dst, act);
-        if (r != BRI_OK) return r;
-        return lincomb(dst, all(1.0), dst, all(L.kl_n == 0 ? rho + mt : mt), v);
-    }
-
-    // dst = approximate A_{k+1}^{-1} v, or v itself below the last level
-    int precondition(int k, const double2 *v, double2 *dst) {
-        if (k + 1 >= (int)lev.size()) return lincomb(dst, all(1.0), v);
+    // *res = approximate A_{k+1}^{-1} v, in dst, or v itself below the last level
+    int precondition(int k, const double2 *v, double2 *dst, const double2 **res) {
+        *res = v;
+        if (k + 1 >= (int)lev.size()) return BRI_OK;
+        *res = dst;
         int it;
         const int r = solve(k + 1, v, dst, it, nullptr);
         // an inner level that stops at its cap (or breaks down after progress) still preconditions
@@ -269,12 +377,11 @@ struct Cascade {
         ++L.calls;
         std::vector<Cols> d;
         int rc;
-        if ((rc = lincomb(x, all(0.0), nullptr)) != BRI_OK) return rc;
-        if ((rc = lincomb(L.r, all(1.0), b)) != BRI_OK) return rc;
-        if ((rc = lincomb(L.r0, all(1.0), b)) != BRI_OK) return rc;
-        if ((rc = lincomb(L.p, all(0.0), nullptr)) != BRI_OK) return rc;
-        if ((rc = lincomb(L.v, all(0.0), nullptr)) != BRI_OK) return rc;
-        if ((rc = dots(1, b, b, nullptr, nullptr, nullptr, nullptr, d)) != BRI_OK) return rc;
+        {
+            Step a = comb(L.r, all(1.0), b);  // r = b, x = 0, <b, b>
+            a.zero = x;
+            if ((rc = run_dots(a, 1, d)) != BRI_OK) return rc;
+        }
         std::vector<double> bn(ncol), rel(ncol, 0.0);
         std::vector<char> active(ncol, 0);
         Cols rho_new(ncol), rho_old(ncol, 1.0), alpha(ncol, 1.0), omega(ncol, 1.0);
@@ -306,10 +413,15 @@ struct Cascade {
             // multi-shift skip it
             Cols one_act(ncol, 0.0);
             for (int c = 0; c < ncol; ++c) one_act[c] = active[c] ? 1.0 : 0.0;
-            if ((rc = lincomb(L.p, one_act, L.r, beta, L.p, mbw, L.v)) != BRI_OK) return rc;
-            if ((rc = precondition(k, L.p, L.ph)) != BRI_OK) return rc;
-            if ((rc = apply_a(L, L.ph, L.v, active)) != BRI_OK) return rc;  // v = A K p
-            if ((rc = dots(1, L.r0, L.v, nullptr, nullptr, nullptr, nullptr, d)) != BRI_OK) return rc;
+            Step a = it == 1 ? comb(L.p, one_act, L.r) : comb(L.p, one_act, L.r, beta, L.p, mbw, L.v);
+            bool lo = feed(a, L, active);
+            if ((rc = run(a, 0, lo)) != BRI_OK) return rc;
+            const double2 *ph, *sh;
+            if ((rc = precondition(k, L.p, L.ph, &ph)) != BRI_OK) return rc;
+            a = Step{};
+            a.out = L.v;
+            a.da[0] = b;
+            if ((rc = apply_a(L, ph, a, active, 1, d)) != BRI_OK) return rc;  // v = A K p, <r0, v>
             Cols ma(ncol, 0.0), half(ncol, 0.0);
             for (int c = 0; c < ncol; ++c) {
                 if (!active[c]) continue;
@@ -323,8 +435,9 @@ struct Cascade {
                 ma[c] = -alpha[c];
             }
             for (int c = 0; c < ncol; ++c) one_act[c] = active[c] ? 1.0 : 0.0;
-            if ((rc = lincomb(L.s, one_act, L.r, ma, L.v)) != BRI_OK) return rc;  // s = r - alpha v
-            if ((rc = dots(1, L.s, L.s, nullptr, nullptr, nullptr, nullptr, d)) != BRI_OK) return rc;
+            a = comb(L.s, one_act, L.r, ma, L.v);  // s = r - alpha v, <s, s>
+            lo = feed(a, L, active);
+            if ((rc = run_dots(a, 1, d, lo)) != BRI_OK) return rc;
             bool any_half = false;
             for (int c = 0; c < ncol; ++c) {
                 if (!active[c]) continue;
@@ -338,16 +451,20 @@ struct Cascade {
                     any_half = true;
                 }
             }
-            if (any_half && (rc = lincomb(x, all(1.0), x, half, L.ph)) != BRI_OK) return rc;
+            if (any_half && (rc = run(comb(x, all(1.0), x, half, ph))) != BRI_OK) return rc;
             if (nact == 0) break;
             if (any_half) {  // the columns that just finished leave s as well
                 for (int c = 0; c < ncol; ++c) one_act[c] = active[c] ? 1.0 : 0.0;
-                if ((rc = lincomb(L.s, one_act, L.s)) != BRI_OK) return rc;
+                a = comb(L.s, one_act, L.s);
+                lo = feed(a, L, active);
+                if ((rc = run(a, 0, lo)) != BRI_OK) return rc;
             }
-            if ((rc = precondition(k, L.s, L.sh)) != BRI_OK) return rc;
-            if ((rc = apply_a(L, L.sh, L.t, active)) != BRI_OK) return rc;  // t = A K s
-            if ((rc = dots(2, L.t, L.s, L.t, L.t, nullptr, nullptr, d)) != BRI_OK) return rc;
-            Cols ax(ncol, 0.0), ox(ncol, 0.0), keep(ncol, 1.0), rs(ncol, 0.0), rt(ncol, 0.0);
+            if ((rc = precondition(k, L.s, L.sh, &sh)) != BRI_OK) return rc;
+            a = Step{};
+            a.out = L.t;
+            a.db[0] = L.s;
+            if ((rc = apply_a(L, sh, a, active, 2, d)) != BRI_OK) return rc;  // t = A K s, <t, s>, <t, t>
+            Coef3 cf{};
             for (int c = 0; c < ncol; ++c) {
                 if (!active[c]) continue;
                 if (d[1][c].real() == 0.0 || !std::isfinite(d[1][c].real())) {
@@ -357,16 +474,16 @@ struct Cascade {
                     continue;
                 }
                 omega[c] = d[0][c] / d[1][c].real();
-                ax[c] = alpha[c];
-                ox[c] = omega[c];
-                keep[c] = 0.0;
-                rs[c] = 1.0;
-                rt[c] = -omega[c];
+                cf.c[c][0] = make_double2(alpha[c].real(), alpha[c].imag());
+                cf.c[c][1] = make_double2(omega[c].real(), omega[c].imag());
+                cf.c[c][2].x = 1.0;
             }
-            if ((rc = lincomb(x, all(1.0), x, ax, L.ph, ox, L.sh)) != BRI_OK) return rc;  // x += alpha Kp + omega Ks
-            if ((rc = lincomb(L.r, keep, L.r, rs, L.s, rt, L.t)) != BRI_OK) return rc;    // r = s - omega t
+            // x += alpha Kp + omega Ks, r = s - omega t, <r, r>, <r0, r>
+            hipLaunchKernelGGL(outer_xr_kernel, dim3(blocks(), ncol), dim3(STEP_THREADS), 0, s, n, cf, x, L.r, ph, sh,
+                               L.s, L.t, b, sums.p);
+            if (hipGetLastError() != hipSuccess) return BRI_EHIP;
             rho_old = rho_new;
-            if ((rc = dots(2, L.r, L.r, L.r0, L.r, nullptr, nullptr, d)) != BRI_OK) return rc;
+            if ((rc = take_dots(2, d)) != BRI_OK) return rc;
             for (int c = 0; c < ncol; ++c) {
                 if (!active[c]) continue;
                 rel[c] = std::sqrt(d[0][c].real()) / bn[c];
@@ -450,12 +567,11 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
     }
     const size_t vb = al256((size_t)12 * g.V * sizeof(double2) * nrhs);
     const size_t nvec = (size_t)NVEC * (nprec + 1) + 1;
-    const size_t pb = al256(sizeof(double) * 2 * 3 * DOT_BLOCKS * nrhs);
     bool f64_kernel = false;
     for (int k = 0; k < nprec; ++k) f64_kernel = f64_kernel || (prec[k].kl_n == 0 && prec[k].inner == BRI_F64);
     const size_t lb = lo_kernel ? al256((size_t)12 * g.V * sizeof(float2) * nrhs) : 0;
     const size_t kb = f64_kernel ? vb : 0;
-    const size_t need = nvec * vb + pb + al256(ovb) + 2 * lb + 2 * kb;
+    const size_t need = nvec * vb + al256(ovb) + 2 * lb + 2 * kb;
     if (!work) {
         *work_bytes = need;
         return BRI_OK;
@@ -480,7 +596,7 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
     c.n = (size_t)12 * g.V;
     c.ncol = nrhs;
     c.s = (hipStream_t)stream;
-    c.hp.resize((size_t)2 * 3 * DOT_BLOCKS * nrhs);
+    if (!c.sums.get((size_t)MAXD * STEP_BLOCKS * nrhs, c.s)) return BRI_EHIP;
     char *base = (char *)work;
     auto take = [&](size_t b) {
         char *p = base;
@@ -504,10 +620,9 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
             L.max_iter = prec[k - 1].max_iter;
             L.kprec = prec[k - 1].kl_n == 0 ? prec[k - 1].inner : BRI_F64;
         }
-        double2 **vs[NVEC] = {&L.r, &L.r0, &L.p, &L.v, &L.s, &L.t, &L.ph, &L.sh};
+        double2 **vs[NVEC] = {&L.r, &L.p, &L.v, &L.s, &L.t, &L.ph, &L.sh};
         for (auto vp : vs) *vp = (double2 *)take(vb);
     }
-    c.partial = (double *)take(pb);
     c.ov = take(al256(ovb));
     c.ov_bytes = ovb;
     if (lo_kernel) {
@@ -525,10 +640,10 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
     Level &top = c.lev[0];
     const std::vector<char> every(nrhs, 1);
     if (mp->complete) {
-        if ((rc = c.apply_d(top, b, top.t, every)) != BRI_OK) return rc;
-        rc = c.lincomb(bt, c.all((1.0 + m / (2.0 * rho)) / den), b, c.all(-m / (4.0 * rho * rho) / den), top.t);
+        if ((rc = c.apply_d(top, b, top.t)) != BRI_OK) return rc;
+        rc = c.run(c.comb(bt, c.all((1.0 + m / (2.0 * rho)) / den), b, c.all(-m / (4.0 * rho * rho) / den), top.t));
     } else {
-        rc = c.lincomb(bt, c.all(1.0 / den), b);
+        rc = c.run(c.comb(bt, c.all(1.0 / den), b));
     }
     if (rc != BRI_OK) return rc;
     int it = 0;
@@ -538,10 +653,11 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
     double true_rel = 0.0;
     {
         std::vector<Cols> d, e;
-        if ((rc = c.dots(1, bt, bt, nullptr, nullptr, nullptr, nullptr, d)) != BRI_OK) return rc;
-        if ((rc = c.apply_a(top, x, top.t, every)) != BRI_OK) return rc;
-        if ((rc = c.lincomb(top.t, c.all(1.0), bt, c.all(-1.0), top.t)) != BRI_OK) return rc;
-        if ((rc = c.dots(1, top.t, top.t, nullptr, nullptr, nullptr, nullptr, e)) != BRI_OK) return rc;
+        Step a{};
+        a.out = top.t;
+        a.da[0] = a.db[0] = bt;
+        if ((rc = c.apply_a(top, x, a, every, 1, d)) != BRI_OK) return rc;
+        if ((rc = c.run_dots(c.comb(top.t, c.all(1.0), bt, c.all(-1.0), top.t), 1, e)) != BRI_OK) return rc;
         for (int k = 0; k < nrhs; ++k) {
             const double bn = std::sqrt(d[0][k].real());
             if (bn > 0.0) true_rel = std::max(true_rel, std::sqrt(e[0][k].real()) / bn);
