@@ -11,6 +11,9 @@ hipError_t launch_f32_bri(const StencilArgs &, bool, int, const StencilConfig &,
 hipError_t launch_f32_wil(const StencilArgs &, bool, int, const StencilConfig &, hipStream_t);
 hipError_t launch_bf16_bri(const StencilArgs &, bool, int, const StencilConfig &, hipStream_t);
 hipError_t launch_bf16_wil(const StencilArgs &, bool, int, const StencilConfig &, hipStream_t);
+hipError_t launch_f64_rows(const StencilArgs &, bool, int, hipStream_t);
+hipError_t launch_f32_rows(const StencilArgs &, bool, int, hipStream_t);
+hipError_t launch_bf16_rows(const StencilArgs &, bool, int, hipStream_t);
 
 // A 64-site tile that divides the lattice.  Column traversal: tile
 // tile[0] x tile[1] x 1 x 1 with colz | Lz.  Otherwise x first (coalescing),
@@ -90,14 +93,16 @@ int plan_tile(const Geom &g, const StencilConfig &cfg, int tile[4], int nb[4]) {
 static int line_tiles(const Geom &g, int n) { return (g.L[1] + n - 1) / n * g.L[2] * g.L[3]; }
 
 int stencil_slots(const Geom &g, const StencilConfig &cfg) {
-    return cfg.small > 0 ? g.V / 16 : cfg.lines > 0 ? line_tiles(g, cfg.lines) : g.V / 64;
+    return cfg.small > 0 ? g.V / 16
+           : cfg.rows > 0 || cfg.lines > 0 ? line_tiles(g, cfg.rows > 0 ? cfg.rows : cfg.lines)
+                                           : g.V / 64;
 }
 
 int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilConfig &cfg, hipStream_t st) {
     if (a.ncol < 1 || a.ncol > 65535) return BRI_EINVAL;
     int rc = BRI_OK;
-    if (cfg.lines > 0) {
-        const int n = cfg.lines;
+    if (cfg.rows > 0 || cfg.lines > 0) {
+        const int n = cfg.rows > 0 ? cfg.rows : cfg.lines;
         a.tile[0] = a.g.L[0];
         a.tile[1] = n;
         a.tile[2] = a.tile[3] = 1;
@@ -116,7 +121,13 @@ int stencil_launch(StencilArgs a, int prec, bool dag, int mode, const StencilCon
     if (a.kind != KERN_BRI && a.kind != KERN_WIL) return BRI_EINVAL;
     const bool wil = a.kind == KERN_WIL;
     hipError_t e;
-    if (prec == BRI_F64)
+    if (cfg.rows > 0)
+        e = wil                     ? hipErrorInvalidValue
+            : prec == BRI_F64       ? launch_f64_rows(a, dag, mode, st)
+            : prec == BRI_F32       ? launch_f32_rows(a, dag, mode, st)
+            : prec == BRI_F32_BF16W ? launch_bf16_rows(a, dag, mode, st)
+                                    : hipErrorInvalidValue;
+    else if (prec == BRI_F64)
         e = wil ? launch_f64_wil(a, dag, mode, cfg, st) : launch_f64_bri(a, dag, mode, cfg, st);
     else if (prec == BRI_F32)
         e = wil ? launch_f32_wil(a, dag, mode, cfg, st) : launch_f32_bri(a, dag, mode, cfg, st);
@@ -256,8 +267,24 @@ static void line_columns(const Geom &g, int lines, int cap, StencilConfig &c) {
         }
 }
 
+// The four-right-hand-side kernel: blocks of exactly 48 sites in whole x-lines, groups of four right-hand
+// sides that are full, or in FP64 lack one (an empty place costs as much as a full one).  24^3x48: FP64 4
+// right-hand sides 3.75 -> 2.9 ms, 7: 6.7 -> 5.6, 12: 10.9 -> 8.5, 6 no gain; FP32 4: 2.33 -> 1.88, 12: 6.7 ->
+// 5.6, 7: 4.0 -> 3.7, 3 slower; bfloat16 links 12: 6.2 -> 5.6, 7 and 3 slower.  12^3x24, 4: FP64 248 -> 202
+// us, FP32 154 -> 140.  In FP32 it needs a block per CU and group (192 tiles, 12 right-hand sides 102
+// against 105 us).  Blocks with idle rows lose (20-site lines: FP32 650 against 1120 us), and so do lines of 16
+// and 32 sites, which the x-line and standard kernels fill (16^3x64, 12: FP64 3.6 against 3.7 ms).  The
+// kernel's 32-bit offsets reach over the 48 staged components.
+static bool rows_fit(const Geom &g, int prec, int ncol) {
+    const int Lx = g.L[0];
+    if (Lx != 12 && Lx != 24 && Lx != 48) return false;
+    if (g.L[1] % (48 / Lx) || g.V > 0xffffffffLL / 48) return false;
+    if (prec == BRI_F64) return ncol >= 3 && (ncol % 4 == 0 || ncol % 4 == 3);
+    return ncol % 4 == 0 && g.V / 48 >= 256;
+}
+
 bool forms_alpha(const StencilConfig &cfg, int ndots) {
-    if (cfg.variant == VAR_TSTREAM || cfg.variant == VAR_MFMA) return false;
+    if (cfg.variant == VAR_TSTREAM || cfg.variant == VAR_MFMA || cfg.rows > 0) return false;
     return ndots <= MAX_DOTS && (cfg.small > 0 || cfg.rpt == 0);
 }
 
@@ -273,6 +300,14 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     if (kind == KERN_BRI && g.V <= SMALL_MAX_SITES && blocks16 <= (prec != BRI_F64 ? 1536 : ncol > 1 ? 512 : 256)) {
         c.small = blocks16 <= 256 ? 8 : 4;
         c.xcd_remap = 1;
+        return;
+    }
+    if (kind == KERN_BRI && rows_fit(g, prec, ncol)) {
+        c = StencilConfig{};
+        c.nsplit = 4;
+        c.xcd_remap = 1;
+        c.rows = 48 / g.L[0];
+        line_columns(g, c.rows, 36, c);
         return;
     }
     int n = 0;
@@ -330,8 +365,8 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     line_columns(g, n, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, c);
 }
 
-// Every launch leaves one pair of sums per tile; a tile holds at least 32 sites, 16 in the small-lattice
-// kernel.
+// Every launch leaves one pair of sums per tile; a tile holds at least 32 sites on average, 16 in the
+// small-lattice kernel.
 int stencil_max_slots(const Geom &g) { return g.V <= SMALL_MAX_SITES ? g.V / 16 : g.V / 32; }
 
 // the configuration a launch uses: the installed one, else the default with whole-line tiles where

@@ -78,6 +78,7 @@ struct StencilConfig {
     int xcd_remap;  // 1 = give each XCD a contiguous range of tiles
     int lines = 0;    // see below
     int small = 0;    // see below
+    int rows = 0;     // see below
     int variant = 0;  // 1-RHS kernel variant (rpt must be 0 for 1 and 2):
                       //   VAR_STANDARD  the 64-site tile kernel above;
                       //   VAR_TSTREAM   t-streaming: xyz tile tile[0..2] (256 sites), chunks of
@@ -95,6 +96,10 @@ struct StencilConfig {
 
 // StencilConfig::small = 4 or 8: the small-lattice kernel of stencil_small.hpp with that many waves on
 // every 16 sites; set by default_config only.
+
+// StencilConfig::rows > 0 replaces all of the above by the four-right-hand-side kernel of
+// stencil_rows.hpp, on tiles of `rows` whole x-lines in the columns of colz and coly; set by
+// default_config only.
 
 enum StencilVariant { VAR_STANDARD = 0, VAR_TSTREAM = 1, VAR_XLINE = 2, VAR_MFMA = 3 };
 

@@ -833,6 +833,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
 
 #include "stencil_mfma.hpp"
 #include "stencil_small.hpp"
+#include "stencil_rows.hpp"
 
 namespace bri {
 
@@ -960,6 +961,30 @@ template <class LS, int NW, bool DAG> inline hipError_t launch_small(const Stenc
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <class LS, bool DAG, int MODE> inline hipError_t launch_rows_mode(const StencilArgs &a, hipStream_t st) {
+    using C = typename Cx<typename LS::R>::T;
+    if (a.g.L[0] * a.tile[1] != ROWS_SITES || a.g.L[1] % a.tile[1]) return hipErrorInvalidValue;
+    const dim3 grid = group_grid(a, (a.ncol + ROWS_RHS - 1) / ROWS_RHS, ROWS_THREADS), block(ROWS_THREADS);
+    hipLaunchKernelGGL((stencil_rows_kernel<LS, DAG, MODE>), grid, block,
+                       2 * (ROWS_PSI + ROWS_LNK) * ROWS_PITCH * sizeof(C), st, a);
+    return hipGetLastError();
+}
+
+// (the adjoint has the plain and the residual-update epilogue, D the others: what the callers launch)
+template <class LS, bool DAG> inline hipError_t launch_rows(const StencilArgs &a, int mode, hipStream_t st) {
+    if (mode == EPI_PLAIN) return launch_rows_mode<LS, DAG, EPI_PLAIN>(a, st);
+    if constexpr (DAG) {
+        if (mode == EPI_CG_R) return launch_rows_mode<LS, DAG, EPI_CG_R>(a, st);
+    } else {
+        if (mode == EPI_NORMS) return launch_rows_mode<LS, DAG, EPI_NORMS>(a, st);
+        if constexpr (std::is_same<LS, LinkF64>::value) {
+            if (mode == EPI_OV) return launch_rows_mode<LS, DAG, EPI_OV>(a, st);
+            if (mode == EPI_SIGN) return launch_rows_mode<LS, DAG, EPI_SIGN>(a, st);
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 template <class LS, bool DAG, int KIND>
