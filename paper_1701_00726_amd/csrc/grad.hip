@@ -114,40 +114,192 @@ struct PairTable {
 };
 
 // G[j][a][b](x) = sum_p w_p sum_t conj((S_d u_p(x))_{t,a}) v_p(x+d)_{t,b}, all d != 0.
-// A workgroup owns 64 consecutive sites and 8 of the 80 displacements (the block index modulo
-// the group count picks which 8, so the ten groups of a tile are dispatched side by side);
-// each wave keeps the 3x3 accumulators of 2 displacements in registers while the pairs stream
-// through, so u_p(x) and the neighbourhood of v_p are read while hot in L2 (a pass per
-// displacement would stream every pair from HBM 80 times).
-// The Wilson operator has only the 8 one-hop displacements (one group), with its own weights.
-constexpr int OUTER_WAVES = 4;
-constexpr int OUTER_PER_WAVE = 2;
-template <int KIND> struct OuterDisp {
-    static constexpr int n = KIND == KERN_WIL ? 8 : 80;
-    static constexpr int groups = n / (OUTER_WAVES * OUTER_PER_WAVE);
-    // displacement index of the jj-th displacement (the centre j = 40 is skipped)
-    __device__ __forceinline__ static int at(int jj) {
-        if constexpr (KIND == KERN_WIL) {
-            const int half = jj < 4 ? jj : 7 - jj;  // 13, 31, 37, 39 and their opposites 67, 49, 43, 41
-            const int j = 40 - (half == 0 ? 27 : half == 1 ? 9 : half == 2 ? 3 : 1);
-            return jj < 4 ? j : 80 - j;
-        }
-        return jj < 40 ? jj : jj + 1;
-    }
-};
+//
+// Brillouin operator.  A wave owns a group of displacements of equal (d_y, d_z, d_t) = (0, ...) + m on 64
+// consecutive sites s and keeps the 3x3 accumulators of its three d_x in registers while the pairs
+// stream through.  Lane s holds those of the output sites s - d_x, so that all three take the same
+// neighbour v(s + m), and with S_d hermitian the spin matrix goes to v, where the three share most of
+// it:  S_d v = a_h v + c_h (R v + d_x gamma_1 v),  R = d_y gamma_2 + d_z gamma_3 + d_t gamma_4.
+// The u(s - d_x) are the same for every group: a block of four waves stages them in LDS, written there
+// by the loads themselves a pair ahead, in two buffers (74 KB: two blocks per CU, two waves a SIMD, 256
+// registers a lane).  A tile's seven blocks are consecutive, so its vectors are read while hot in one
+// XCD's L2.
+// 33 pairs at 16^4 3.44 -> 2.43 ms (31 TFLOP/s), 2 pairs at 12^3x24 204 -> 142 us; before, a wave took two
+// displacements with the spin matrix on u, 18 loads a displacement and pair where it is now 7, and
+// one wave a SIMD.  What bounds it now: the FP64 multiply-adds (1.1 ms at 16^4) and, with two waves a
+// SIMD, the latency of v and of the LDS reads between them.
+constexpr int LINE_WAVES = 4;
+constexpr int LINE_BLOCKS = 7;  // blocks per tile: 27 groups, the last wave idle
+constexpr int LINE_ROWS = 36;   // staged: three d_x x twelve components
 
-template <int KIND>
-__global__ __launch_bounds__(64 * OUTER_WAVES) void grad_outer_kernel(Geom g, PairTable pt,
-                                                                      double2 *__restrict__ G) {
-    constexpr int GROUPS = OuterDisp<KIND>::groups;
+// acc[d_x][a][b] += conj(u_{T,a}) (S_d v)_{T,b} for the three d_x and spin T; u in rows of 64 lanes
+template <int T>
+__device__ __forceinline__ void outer_row(double2 (&acc)[3][3][3], const double2 (&v)[4][3], const double2 (*u)[64],
+                                          int lane, double a0, double a1, double c0, double c1, double d1, double d2,
+                                          double d3) {
+    constexpr int X = 3 - T, Z = T ^ 2;        // the spins gamma_1, gamma_2 and gamma_3, gamma_4 take row T from
+    constexpr double G1 = T < 2 ? -1.0 : 1.0;  // gamma_1: i G1
+    constexpr double G2 = T == 0 || T == 3 ? -1.0 : 1.0;
+    constexpr double G3 = T == 0 || T == 3 ? -1.0 : 1.0;  // gamma_3: i G3
+    auto add = [&](auto I, const double2(&f)[3]) {
+        constexpr int i = decltype(I)::value;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double2 x = u[i * 12 + T * 3 + a][lane];
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                acc[i][a][b].x += x.x * f[b].x + x.y * f[b].y;
+                acc[i][a][b].y += x.x * f[b].y - x.y * f[b].x;
+            }
+        }
+        // (the sums are formed here: left to the compiler, all rows of u are read first and spill)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            asm volatile("" : "+v"(acc[i][a][0].x), "+v"(acc[i][a][0].y), "+v"(acc[i][a][1].x), "+v"(acc[i][a][1].y),
+                         "+v"(acc[i][a][2].x), "+v"(acc[i][a][2].y) : : "memory");
+    };
+    double2 r[3], f[3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        r[b] = make_double2(G2 * d1 * v[X][b].x, G2 * d1 * v[X][b].y);
+        axpy_ic(r[b], G3 * d2, v[Z][b]);
+        axpy_c(r[b], d3, v[Z][b]);
+        f[b] = make_double2(a0 * v[T][b].x, a0 * v[T][b].y);
+        axpy_c(f[b], c0, r[b]);
+        r[b] = make_double2(c1 * r[b].x, c1 * r[b].y);
+        axpy_c(r[b], a1, v[T][b]);
+    }
+    add(std::integral_constant<int, 1>{}, f);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        f[b] = r[b];
+        axpy_ic(f[b], -G1 * c1, v[X][b]);
+    }
+    add(std::integral_constant<int, 0>{}, f);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) axpy_ic(r[b], G1 * c1, v[X][b]);
+    add(std::integral_constant<int, 2>{}, r);
+}
+
+__global__ __launch_bounds__(64 * LINE_WAVES, 2) void grad_outer_kernel(Geom g, PairTable pt, double2 *__restrict__ G) {
+    extern __shared__ __align__(16) unsigned char outer_lds[];
+    double2(*us)[LINE_ROWS][64] = (double2(*)[LINE_ROWS][64])outer_lds;  // [2]
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned lin = xcd_order(blockIdx.x, gridDim.x, 1);
-    const unsigned grp = lin % GROUPS;
-    const unsigned x = (lin / GROUPS) * 64 + lane;
+    const unsigned tile = lin / LINE_BLOCKS;
+    const int m = (int)(lin - tile * LINE_BLOCKS) * LINE_WAVES + w;  // the group; 27: none
+    const size_t V = (size_t)g.V;
+    const bool live = tile * 64 + lane < (unsigned)g.V;
+    const unsigned site = live ? tile * 64 + lane : (unsigned)g.V - 1;
+    const int e1 = m % 3 - 1, e2 = (m / 3) % 3 - 1, e3 = m / 9 - 1;
+    unsigned xs[3], ys;  // the sites s - d_x and s + m
+    {
+        int c[4], s = (int)site;
+        for (int mu = 0; mu < 4; ++mu) {
+            c[mu] = s % g.L[mu];
+            s /= g.L[mu];
+        }
+        const unsigned x0 = site - c[0];
+        xs[0] = x0 + wrapc(c[0] + 1, g.L[0]);
+        xs[1] = site;
+        xs[2] = x0 + wrapc(c[0] - 1, g.L[0]);
+        c[1] = wrapc(c[1] + e1, g.L[1]);
+        c[2] = wrapc(c[2] + e2, g.L[2]);
+        c[3] = m < 27 ? wrapc(c[3] + e3, g.L[3]) : c[3];
+        ys = site_of(g, c);
+    }
+    const int h = (e1 != 0) + (e2 != 0) + (e3 != 0);
+    const double la0 = lap_weight(h), la1 = lap_weight(h + 1), lc0 = iso_weight(h), lc1 = iso_weight(h + 1);
+    // 32-bit byte offsets on a uniform base (G alone is 11664 bytes a site)
+    const unsigned xo[3] = {xs[0] * 16u, xs[1] * 16u, xs[2] * 16u}, yo = ys * 16u;
+    // rows w, w + 4, ... of the 36 are this wave's to stage
+    auto stage = [&](int p) {
+        const char *__restrict__ up = (const char *)pt.u[p];
+        double2(*to)[64] = us[p & 1];
+#pragma unroll
+        for (int k = 0; k < LINE_ROWS / LINE_WAVES; ++k) {
+            const int row = k * LINE_WAVES + w, comp = row % 12;  // 12 rows are three k
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(up + (size_t)comp * V * sizeof(double2) + xo[k / 3]),
+                (__attribute__((address_space(3))) void *)&to[row][0], 16, 0, 0);
+        }
+    };
+    double2 acc[3][3][3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) acc[i][a][b] = make_double2(0.0, 0.0);
+    double2 v[4][3];
+    auto load_v = [&](int p) {
+        const char *__restrict__ vp = (const char *)pt.v[p];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) v[t][b] = *(const double2 *)(vp + (size_t)(t * 3 + b) * V * sizeof(double2) + yo);
+    };
+    if (pt.n > 0) {
+        stage(0);
+        load_v(0);
+    }
+#pragma unroll 1
+    for (int p = 0; p < pt.n; ++p) {
+        // pair p is staged and its v here, and no wave still reads the buffer of pair p - 1
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+        __syncthreads();
+        if (p + 1 < pt.n) stage(p + 1);
+        if (m >= 27) continue;
+        const double wp = pt.w[p];
+        const double a0 = wp * la0, a1 = wp * la1, c0 = wp * lc0, c1 = wp * lc1;
+        const double2(*u)[64] = us[p & 1];
+        outer_row<0>(acc, v, u, lane, a0, a1, c0, c1, (double)e1, (double)e2, (double)e3);
+        outer_row<1>(acc, v, u, lane, a0, a1, c0, c1, (double)e1, (double)e2, (double)e3);
+        outer_row<2>(acc, v, u, lane, a0, a1, c0, c1, (double)e1, (double)e2, (double)e3);
+        outer_row<3>(acc, v, u, lane, a0, a1, c0, c1, (double)e1, (double)e2, (double)e3);
+        if (p + 1 < pt.n) load_v(p + 1);  // the other block's wave computes under this
+    }
+    if (!live || m >= 27) return;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        if (i == 1 && m == 13) continue;  // d = 0
+#pragma unroll
+        for (int aa = 0; aa < 3; ++aa)
+#pragma unroll
+            for (int bb = 0; bb < 3; ++bb) {
+                double2 *gp = G + ((size_t)(3 * m + i) * 9 + aa * 3 + bb) * V + xs[i];
+                if (pt.accumulate) {
+                    const double2 o = *gp;
+                    *gp = make_double2(o.x + acc[i][aa][bb].x, o.y + acc[i][aa][bb].y);
+                } else {
+                    *gp = acc[i][aa][bb];
+                }
+            }
+    }
+}
+
+// The Wilson operator has only the 8 one-hop displacements, with its own weights: a workgroup owns 64
+// consecutive sites, each wave the 3x3 accumulators of 2 of them.
+constexpr int OUTER_WAVES = 4;
+constexpr int OUTER_PER_WAVE = 2;
+
+// displacement index of the jj-th one-hop displacement: 13, 31, 37, 39 and their opposites 67, 49, 43, 41
+__device__ __forceinline__ int one_hop(int jj) {
+    const int half = jj < 4 ? jj : 7 - jj;
+    const int j = 40 - (half == 0 ? 27 : half == 1 ? 9 : half == 2 ? 3 : 1);
+    return jj < 4 ? j : 80 - j;
+}
+
+__global__ __launch_bounds__(64 * OUTER_WAVES) void grad_outer_wil_kernel(Geom g, PairTable pt,
+                                                                          double2 *__restrict__ G) {
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned lin = xcd_order(blockIdx.x, gridDim.x, 1);
+    const unsigned x = lin * 64 + lane;
     const bool live = x < (unsigned)g.V;
     const size_t V = (size_t)g.V;
-    const int jbase = (grp * OUTER_WAVES + w) * OUTER_PER_WAVE;
+    const int jbase = w * OUTER_PER_WAVE;
     int cx[4];
     {
         int s = live ? (int)x : 0;
@@ -159,7 +311,7 @@ __global__ __launch_bounds__(64 * OUTER_WAVES) void grad_outer_kernel(Geom g, Pa
     unsigned ys[OUTER_PER_WAVE];
 #pragma unroll
     for (int i = 0; i < OUTER_PER_WAVE; ++i) {
-        const int j = OuterDisp<KIND>::at(jbase + i);
+        const int j = one_hop(jbase + i);
         int cy[4];
 #pragma unroll
         for (int mu = 0; mu < 4; ++mu) cy[mu] = wrapc(cx[mu] + dj(j, mu), g.L[mu]);
@@ -187,7 +339,7 @@ __global__ __launch_bounds__(64 * OUTER_WAVES) void grad_outer_kernel(Geom g, Pa
             }
 #pragma unroll
         for (int i = 0; i < OUTER_PER_WAVE; ++i) {
-            const DirW<double, false, KIND> dw(OuterDisp<KIND>::at(jbase + i));  // S_d of the kernel
+            const DirW<double, false, KERN_WIL> dw(one_hop(jbase + i));  // S_d of the kernel
             double2 e[4][3];
 #pragma unroll
             for (int s = 0; s < 4; ++s)
@@ -212,7 +364,7 @@ __global__ __launch_bounds__(64 * OUTER_WAVES) void grad_outer_kernel(Geom g, Pa
     }
 #pragma unroll
     for (int i = 0; i < OUTER_PER_WAVE; ++i) {
-        const int j = OuterDisp<KIND>::at(jbase + i);
+        const int j = one_hop(jbase + i);
 #pragma unroll
         for (int aa = 0; aa < 3; ++aa)
 #pragma unroll
@@ -427,11 +579,10 @@ static size_t grad_g_bytes(const Geom &g) { return al256((size_t)81 * 9 * g.V * 
 static void outer_pairs(const Geom &g, const PairTable &pt, double2 *G, hipStream_t s, int kind) {
     const int tiles = (g.V + 63) / 64;
     if (kind == KERN_WIL)
-        hipLaunchKernelGGL(grad_outer_kernel<KERN_WIL>, dim3(OuterDisp<KERN_WIL>::groups * tiles),
-                           dim3(64 * OUTER_WAVES), 0, s, g, pt, G);
+        hipLaunchKernelGGL(grad_outer_wil_kernel, dim3(tiles), dim3(64 * OUTER_WAVES), 0, s, g, pt, G);
     else
-        hipLaunchKernelGGL(grad_outer_kernel<KERN_BRI>, dim3(OuterDisp<KERN_BRI>::groups * tiles),
-                           dim3(64 * OUTER_WAVES), 0, s, g, pt, G);
+        hipLaunchKernelGGL(grad_outer_kernel, dim3(LINE_BLOCKS * tiles), dim3(64 * LINE_WAVES),
+                           2 * LINE_ROWS * 64 * sizeof(double2), s, g, pt, G);
 }
 
 // pull-back of the accumulated G through the path average (Brillouin kernel) and the force
