@@ -145,11 +145,11 @@ struct LinkBF16 {
 
 // Launch order -> logical block with remap: consecutive blocks go to the 8 XCDs in turn, so XCD k gets
 // the blocks k, k + 8, ...; numbering those consecutively gives each XCD one contiguous range (the first
-// nblk % 8 XCDs one block more).
-__device__ __forceinline__ int xcd_order(int blk, int nblk, int remap) {
-    if (!remap) return blk;
-    const int k = blk & 7, more = nblk & 7;
-    return k * (nblk >> 3) + (k < more ? k : more) + (blk >> 3);
+// nblk % 8 XCDs one block more), from its end with reverse.
+__device__ __forceinline__ int xcd_order(int blk, int nblk, int remap, bool reverse = false) {
+    if (!remap) return reverse ? nblk - 1 - blk : blk;
+    const int k = blk & 7, more = nblk & 7, mine = (nblk >> 3) + (k < more ? 1 : 0), i = blk >> 3;
+    return k * (nblk >> 3) + (k < more ? k : more) + (reverse ? mine - 1 - i : i);
 }
 
 // ---------------------------------------------------------------- launches

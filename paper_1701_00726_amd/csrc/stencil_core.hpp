@@ -224,9 +224,9 @@ __device__ __forceinline__ unsigned tile_site(const Geom &g, const int tile[4], 
 // rest follow in blockIdx.y), so that after the XCD ordering the blocks that read the same links
 // run together on one XCD and share those links in its L2 instead of re-reading them from HBM or
 // the Infinity Cache one pass over the lattice later.
-__device__ __forceinline__ void tile_and_group(int ntiles, int remap, int &blk, int &grp) {
+__device__ __forceinline__ void tile_and_group(int ntiles, int remap, int &blk, int &grp, bool reverse = false) {
     const int gin = gridDim.x / ntiles;
-    const int lin = xcd_order(blockIdx.x, gridDim.x, remap);
+    const int lin = xcd_order(blockIdx.x, gridDim.x, remap, reverse);
     blk = lin / gin;
     grp = blockIdx.y * gin + (lin - blk * gin);
 }
@@ -247,12 +247,12 @@ __device__ __forceinline__ void clover_row(typename Cx<typename LS::R>::T &v,
 }
 
 // stored slabs a kernel walks: all 40 (Brillouin), or the one-hop slabs j = 40 - 3^(3-k) (Wilson:
-// displacements -t, -z, -y, -x)
+// displacements -t, -z, -y, -x), the last first with reverse
 template <int KIND> struct Slabs {
     static constexpr int n = KIND == KERN_WIL ? 4 : 40;
-    __device__ __forceinline__ static int at(int k) {
+    __device__ __forceinline__ static int at(int k, bool reverse) {
         if constexpr (KIND == KERN_WIL) return 40 - (k == 0 ? 27 : k == 1 ? 9 : k == 2 ? 3 : 1);
-        return k;
+        return reverse ? n - 1 - k : k;
     }
 };
 

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     using C = typename Cx<R>::T;
     constexpr int NFIN = NSPLIT > 4 ? 4 : NSPLIT, NCOMP = 12 / NFIN;
     int blk, col;
-    tile_and_group(a.nslots, a.xcd_remap, blk, col);
+    tile_and_group(a.nslots, a.xcd_remap, blk, col, a.reverse);
     if (col >= a.ncol || col_done<MODE>(a, col)) return;  // whole block: this column has converged
 
     const unsigned V = (unsigned)a.g.V;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     }
 
     for (int k = q; k < Slabs<KIND>::n; k += NSPLIT) {
-        const int j = Slabs<KIND>::at(k);
+        const int j = Slabs<KIND>::at(k, a.reverse);
         const DirW<R, DAG, KIND> dw(j);
         const typename LS::store_t *__restrict__ Wj = W + (size_t)j * 9 * V;
         C chi[4][3];
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
     using S = typename LS::store_t;
     constexpr int NFIN = NSPLIT > 4 ? 4 : NSPLIT, NCOMP = 12 / NFIN;
     int blk, col;
-    tile_and_group(a.nslots, a.xcd_remap, blk, col);
+    tile_and_group(a.nslots, a.xcd_remap, blk, col, a.reverse);
     if (col >= a.ncol || col_done<MODE>(a, col)) return;
 
     const unsigned V = (unsigned)a.g.V;
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(64 * MRHS_SPLIT) void stencil_xline_mrhs_kernel(Ste
     const int lane = threadIdx.x & 63;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int blk, grp;
-    tile_and_group(a.nslots, a.xcd_remap, blk, grp);
+    tile_and_group(a.nslots, a.xcd_remap, blk, grp, a.reverse);
     const int col0 = grp * R;
     bool live[R];
     bool any = false;
@@ -716,7 +716,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
     const int lane = threadIdx.x & 63;
     const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int blk, grp;
-    tile_and_group(a.nslots, a.xcd_remap, blk, grp);
+    tile_and_group(a.nslots, a.xcd_remap, blk, grp, a.reverse);
     const int col0 = grp * R;
     // block-uniform: every wave of the block carries the same R columns
     bool live[R];
@@ -751,7 +751,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
             }
 
     for (int k = q; k < Slabs<KIND>::n; k += NSPLIT) {
-        const int j = Slabs<KIND>::at(k);
+        const int j = Slabs<KIND>::at(k, a.reverse);
         const DirW<RT, DAG, KIND> dw(j);
         const typename LS::store_t *__restrict__ Wj = W + (size_t)j * 9 * V;
         C wl[3][3];

@@ -101,7 +101,7 @@ void stencil_rows_kernel(StencilArgs a) {
     extern __shared__ __align__(16) unsigned char rows_lds[];
 
     int blk, grp;
-    tile_and_group(a.nslots, a.xcd_remap, blk, grp);
+    tile_and_group(a.nslots, a.xcd_remap, blk, grp, a.reverse);
     const int col0 = grp * ROWS_RHS;
     const int nlive = a.ncol - col0 < ROWS_RHS ? a.ncol - col0 : ROWS_RHS;
     if (nlive <= 0) return;

@@ -101,3 +101,22 @@ def test_alpha_formed_by_the_stencil(L):
     four, _ = bri.OverlapOp(L, W, kl_n=4, tol=1e-12, nrhs=4).apply(b)
     one, _ = bri.OverlapOp(L, W, kl_n=4, tol=1e-12, nrhs=1).apply(b[2:3].contiguous())
     assert rel_l2(bri.spinor_to_host(one)[0], bri.spinor_to_host(four)[2]) < 1e-10
+
+
+@pytest.mark.parametrize("prec,L,nrhs", [(bri.F64, (16, 16, 16, 14), 1), (bri.F64, (16, 16, 16, 14), 2),
+                                         (bri.F32, (24, 14, 16, 18), 4), (bri.F32, (30, 12, 16, 17), 1)])
+def test_adjoint_backwards(prec, L, nrhs):
+    """Links between 256 and 512 MiB: the adjoint walks tiles and slabs backwards; <x, D y> = <D^dag x, y>
+    for vectors of unit variance holds to the operator's tolerance times |x| |D y|."""
+    need_gpu()
+    V = int(np.prod(L))
+    assert (256 << 20) < V * 360 * (16 if prec == bri.F64 else 8) <= (512 << 20)
+    W = bri.build_links(L, bri.links_to_device(synth.random_links(L, 0.6, 5900)), prec)
+    x, y = (bri.spinor_to_device(synth.gaussian_source(L, 5901 + k, nrhs=nrhs), prec) for k in (0, 1))
+    print(f"[lines] adjoint {L} prec {prec}", flush=True)
+    Dy, Dx = (bri.spinor_to_host(f(L, W, prec, -0.9, v)).astype(complex)
+              for f, v in ((bri.apply, y), (bri.apply_dag, x)))
+    hx, hy = bri.spinor_to_host(x).astype(complex), bri.spinor_to_host(y).astype(complex)
+    for r in range(nrhs):
+        bound = np.linalg.norm(hx[r]) * np.linalg.norm(Dy[r])
+        assert abs(np.vdot(hx[r], Dy[r]) - np.vdot(Dx[r], hy[r])) < (1e-14 if prec == bri.F64 else 2e-6) * bound
