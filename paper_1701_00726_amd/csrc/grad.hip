@@ -445,13 +445,22 @@ __global__ __launch_bounds__(128) void grad_level_kernel(Geom g, const double2 *
 
 // G_U_mu(z) from every level's first step, then F^a_mu(z) = -Im tr(lambda_a U G_U^T) / 2
 // (kind = KERN_WIL: only the one-hop displacements carry a coefficient, and their remainder link
-// is the identity)
-__global__ __launch_bounds__(128) void grad_force_kernel(Geom g, const double2 *__restrict__ U,
-                                                         const double2 *__restrict__ W, const double2 *__restrict__ G,
-                                                         double *__restrict__ F, double2 *__restrict__ GUo, int kind) {
+// is the identity).
+// A block takes 64 sites z and one link direction mu, and its waves share the 27 remainders r (r_mu = 0) of
+// the displacements r +- e_mu; the mu of a site range follow each other on one XCD.  A single wave for all 27
+// left 2.5 waves a SIMD at 12^3x24; the loads in flight bound it (both steps' operands, 212 registers, two
+// waves a SIMD: fewer registers for three or four waves are slower): 332 -> 262 us there, 16^4 488 -> 413
+// (717 MB of G and W at 12^3x24: 163 us at the copy rate; G is read for up to four mu).
+constexpr int FORCE_WAVES = 3;
+__global__ __launch_bounds__(64 * FORCE_WAVES) void grad_force_kernel(Geom g, const double2 *__restrict__ U,
+                                                                      const double2 *__restrict__ W,
+                                                                      const double2 *__restrict__ G,
+                                                                      double *__restrict__ F,
+                                                                      double2 *__restrict__ GUo, int kind) {
     const unsigned lin = xcd_order(blockIdx.x, gridDim.x, 1);
-    const unsigned z = (lin >> 2) * blockDim.x + threadIdx.x;
-    if (z >= (unsigned)g.V) return;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const bool live = (lin >> 2) * 64 + lane < (unsigned)g.V;
+    const unsigned z = live ? (lin >> 2) * 64 + lane : (unsigned)g.V - 1;
     const size_t V = (size_t)g.V;
     int cz[4];
     {
@@ -461,37 +470,34 @@ __global__ __launch_bounds__(128) void grad_force_kernel(Geom g, const double2 *
             s /= g.L[mu];
         }
     }
+    const int mu = lin & 3;
+    double2 GU[3][3];
+    for (int a = 0; a < 3; ++a)
+        for (int b = 0; b < 3; ++b) GU[a][b] = make_double2(0.0, 0.0);
     {
-        const int mu = lin & 3;  // one thread per (site, link direction); mu varies fastest
-        double2 GU[3][3];
-        for (int a = 0; a < 3; ++a)
-            for (int b = 0; b < 3; ++b) GU[a][b] = make_double2(0.0, 0.0);
         const int emu = mu == 0 ? 1 : mu == 1 ? 3 : mu == 2 ? 9 : 27;
-        int cp[4] = {cz[0], cz[1], cz[2], cz[3]};
-        cp[mu] = wrapc(cp[mu] + 1, g.L[mu]);
+        int cp[4];
+        for (int nu = 0; nu < 4; ++nu) cp[nu] = nu == mu ? wrapc(cz[nu] + 1, g.L[nu]) : cz[nu];
         const unsigned ps = site_of(g, cp);
         // + step at z: T = sg U_mu(z); G_T = (1/k) G_d(z) W_{d - e_mu}(z + e_mu)^T, G_U += sg G_T
         const double sgp = (g.tbc && mu == 3 && cz[3] == g.L[3] - 1) ? -1.0 : 1.0;
         // - step at z + e_mu: T = sg U_mu(z)^dag; G_T = (1/k) G_d(z+e) W_{d + e_mu}(z)^T, G_U += sg G_T^dag
         const double sgm = (g.tbc && mu == 3 && cp[3] == 0) ? -1.0 : 1.0;
-        for (int jd = 0; jd < 81; ++jd) {
-            const int dmu = dj(jd, mu);
-            if (dmu == 0) continue;
-            int k = 0;
-            for (int nu = 0; nu < 4; ++nu) k += dj(jd, nu) != 0;
-            if (kind == KERN_WIL && k != 1) continue;
+        for (int i = w; i < 27; i += FORCE_WAVES) {
+            if (kind == KERN_WIL && i != 13) continue;
+            int jr = 40, k = 1, rest = i;
+            for (int nu = 0, st = 1; nu < 4; ++nu, st *= 3) {
+                if (nu == mu) continue;
+                jr += (rest % 3 - 1) * st;
+                k += rest % 3 != 1;
+                rest /= 3;
+            }
             const double invk = 1.0 / (double)k;
             double2 Gd[3][3], Wr[3][3];
-            if (dmu > 0) {
-                for (int a = 0; a < 3; ++a)
-                    for (int b = 0; b < 3; ++b) Gd[a][b] = G[((size_t)jd * 9 + a * 3 + b) * V + z];
-                link_any(g, W, jd - emu, cp, Wr);
-            } else {
-                for (int a = 0; a < 3; ++a)
-                    for (int b = 0; b < 3; ++b) Gd[a][b] = G[((size_t)jd * 9 + a * 3 + b) * V + ps];
-                link_any(g, W, jd + emu, cz, Wr);
-            }
-            // GT = Gd Wr^T
+            for (int a = 0; a < 3; ++a)
+                for (int b = 0; b < 3; ++b) Gd[a][b] = G[((size_t)(jr + emu) * 9 + a * 3 + b) * V + z];
+            link_any(g, W, jr, cp, Wr);
+            // G_U += Gd Wr^T
             for (int a = 0; a < 3; ++a)
                 for (int b = 0; b < 3; ++b) {
                     double2 t = make_double2(0.0, 0.0);
@@ -500,15 +506,37 @@ __global__ __launch_bounds__(128) void grad_force_kernel(Geom g, const double2 *
                         t.x += m.x;
                         t.y += m.y;
                     }
-                    if (dmu > 0) {
-                        GU[a][b].x += sgp * invk * t.x;
-                        GU[a][b].y += sgp * invk * t.y;
-                    } else {  // dagger: G_U[b][a] += conj(t)
-                        GU[b][a].x += sgm * invk * t.x;
-                        GU[b][a].y -= sgm * invk * t.y;
+                    GU[a][b].x += sgp * invk * t.x;
+                    GU[a][b].y += sgp * invk * t.y;
+                }
+            for (int a = 0; a < 3; ++a)
+                for (int b = 0; b < 3; ++b) Gd[a][b] = G[((size_t)(jr - emu) * 9 + a * 3 + b) * V + ps];
+            link_any(g, W, jr, cz, Wr);
+            // G_U += (Gd Wr^T)^dag
+            for (int a = 0; a < 3; ++a)
+                for (int b = 0; b < 3; ++b) {
+                    double2 t = make_double2(0.0, 0.0);
+                    for (int c = 0; c < 3; ++c) {
+                        const double2 m = cmul(Gd[a][c], Wr[b][c]);
+                        t.x += m.x;
+                        t.y += m.y;
                     }
+                    GU[b][a].x += sgm * invk * t.x;
+                    GU[b][a].y -= sgm * invk * t.y;
                 }
         }
+    }
+    __shared__ double2 part[FORCE_WAVES - 1][9][64];
+    if (w > 0)
+        for (int e = 0; e < 9; ++e) part[w - 1][e][lane] = GU[e / 3][e % 3];
+    __syncthreads();
+    if (w > 0 || !live) return;
+    for (int v = 0; v < FORCE_WAVES - 1; ++v)
+        for (int e = 0; e < 9; ++e) {
+            GU[e / 3][e % 3].x += part[v][e][lane].x;
+            GU[e / 3][e % 3].y += part[v][e][lane].y;
+        }
+    {
         // P = U G_U^T ; F^a = -Im tr(lambda_a P) / 2
         double2 Um[3][3], P[3][3];
         for (int a = 0; a < 3; ++a)
@@ -589,10 +617,10 @@ static void outer_pairs(const Geom &g, const PairTable &pt, double2 *G, hipStrea
 static int force_from_outer(const Geom &g, const double2 *U, const double2 *W, double2 *G, double *F, double2 *GU,
                             hipStream_t s, int kind) {
     const int threads = 128;
-    const int blocks = (g.V + threads - 1) / threads;
+    const int blocks = (g.V + threads - 1) / threads, tiles = (g.V + 63) / 64;
     if (kind == KERN_WIL) {
         // one-hop displacements only: no pull-back through the path average
-        hipLaunchKernelGGL(grad_force_kernel, dim3(4 * blocks), dim3(threads), 0, s, g, U, W, G, F, GU, kind);
+        hipLaunchKernelGGL(grad_force_kernel, dim3(4 * tiles), dim3(64 * FORCE_WAVES), 0, s, g, U, W, G, F, GU, kind);
         return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
     }
     for (int k = 4; k >= 2; --k) {
@@ -604,7 +632,7 @@ static int force_from_outer(const Geom &g, const double2 *U, const double2 *W, d
         }
         hipLaunchKernelGGL(grad_level_kernel, dim3(lower.n * blocks), dim3(threads), 0, s, g, U, G, k, lower);
     }
-    hipLaunchKernelGGL(grad_force_kernel, dim3(4 * blocks), dim3(threads), 0, s, g, U, W, G, F, GU, kind);
+    hipLaunchKernelGGL(grad_force_kernel, dim3(4 * tiles), dim3(64 * FORCE_WAVES), 0, s, g, U, W, G, F, GU, kind);
     return hipGetLastError() == hipSuccess ? BRI_OK : BRI_EHIP;
 }
 
