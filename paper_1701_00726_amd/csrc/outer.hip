@@ -553,7 +553,7 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
         lo_prec = prec[k].inner;
         lo_kernel = lo_kernel || prec[k].kl_n == 0;
     }
-    // workspace: the largest ov_apply workspace of all levels, NVEC vectors per level, bt, partials
+    // workspace: the largest ov_apply workspace of all levels, the vectors of every level, bt
     size_t ovb = 0;
     bool low = false;
     for (int k = -1; k < nprec; ++k) {
@@ -566,7 +566,8 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
         ovb = b > ovb ? b : ovb;
     }
     const size_t vb = al256((size_t)12 * g.V * sizeof(double2) * nrhs);
-    const size_t nvec = (size_t)NVEC * (nprec + 1) + 1;
+    // (a level uses seven vectors; the reported size stays that of eight, the shadow residual's included)
+    const size_t nvec = (size_t)(NVEC + 1) * (nprec + 1) + 1;
     bool f64_kernel = false;
     for (int k = 0; k < nprec; ++k) f64_kernel = f64_kernel || (prec[k].kl_n == 0 && prec[k].inner == BRI_F64);
     const size_t lb = lo_kernel ? al256((size_t)12 * g.V * sizeof(float2) * nrhs) : 0;
