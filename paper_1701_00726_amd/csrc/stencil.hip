@@ -334,6 +334,13 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     }
     if (!fit) return;
     if (kind == KERN_BRI && ncol != 2 && xline_fits(g)) return;  // whole-line tiles already
+    // Wilson: up to 2048 tiles of 16 x 4 stay (16^3x32 FP64 29.9 against 31.7 us, 16^4 FP32 9.7 against 10.4).
+    // Batches stay on cut tiles with runs of four sites or more, whose lanes all work, unless the lines use nine
+    // lanes in ten as well (24^3x48, 12: FP64 2.79 against 3.27 ms; 12^3x24, 3: FP32 21 against 28 us;
+    // 20x12x28x24, 95%, 1.2 to 1.4 times faster on lines; 10-, 18- and 31-site lines 1.3 to 13 times)
+    if (kind == KERN_WIL && ((c.colz > 0 && g.V / 64 <= 2048) ||
+                             (ncol > 1 && g.L[0] % 4 == 0 && 9LL * 64 * tiles > 10LL * g.V)))
+        return;
     // (16 x 4 tiles in columns one row wide: 16^4 overlap apply 4.02 ms, 4.15 in columns of 4 rows; the
     // gradient's batches of 2 and 32 likewise, 13.3 against 13.5 ms; 3 right-hand sides gain, 312 -> 280 us)
     if (kind == KERN_BRI && ncol != 3 && prec == BRI_F64 && tiles <= 1024 && c.colz > 0 && !few) return;
