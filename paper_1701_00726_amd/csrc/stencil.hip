@@ -99,10 +99,10 @@ int stencil_slots(const Geom &g, const StencilConfig &cfg) {
 }
 
 // The solvers apply D and D^dag in turn.  Links larger than the 256 MiB last-level cache, but not by much,
-// are read by each in the order in which the other has pushed them out; with the adjoint walking tiles and
-// slabs backwards each finds what the other read last.  16 iterations of the multi-shift CG: 16^4 (360
-// MiB) 3.35 -> 3.23 ms, 12^3x32 (303) 3.34 -> 3.23; 24^2x12x16 (607) 5.89 -> 5.95, 32^3x64 5% slower, and
-// below the cache's size (12^3x24, 227) no difference.
+// are read by each in the order in which the other has pushed them out; with the adjoint walking the tiles
+// backwards each finds what the other read last.  16 iterations of the multi-shift CG: 16^4 (360 MiB) 3.26 ->
+// 3.20 ms, 12^3x32 (303) 3.30 -> 3.25; 24^2x12x16 (607) 5.89 -> 5.95, 32^3x64 5% slower, and below the
+// cache's size (12^3x24, 227) no difference.
 static bool reverse_pays(const Geom &g, int prec) {
     const long long bytes = 360LL * g.V * (prec == BRI_F64 ? 16 : prec == BRI_F32 ? 8 : 4);
     return bytes > 256LL << 20 && bytes <= 512LL << 20;

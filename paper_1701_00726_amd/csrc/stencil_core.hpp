@@ -247,12 +247,13 @@ __device__ __forceinline__ void clover_row(typename Cx<typename LS::R>::T &v,
 }
 
 // stored slabs a kernel walks: all 40 (Brillouin), or the one-hop slabs j = 40 - 3^(3-k) (Wilson:
-// displacements -t, -z, -y, -x), the last first with reverse
+// displacements -t, -z, -y, -x).  (In order, so that the loads of a slab are addressed by induction: with the
+// order chosen at run time the compiler spreads them between the multiply-adds.)
 template <int KIND> struct Slabs {
     static constexpr int n = KIND == KERN_WIL ? 4 : 40;
-    __device__ __forceinline__ static int at(int k, bool reverse) {
+    __device__ __forceinline__ static int at(int k) {
         if constexpr (KIND == KERN_WIL) return 40 - (k == 0 ? 27 : k == 1 ? 9 : k == 2 ? 3 : 1);
-        return reverse ? n - 1 - k : k;
+        return k;
     }
 };
 

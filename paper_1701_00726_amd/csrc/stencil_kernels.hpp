@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
     }
 
     for (int k = q; k < Slabs<KIND>::n; k += NSPLIT) {
-        const int j = Slabs<KIND>::at(k, a.reverse);
+        const int j = Slabs<KIND>::at(k);
         const DirW<R, DAG, KIND> dw(j);
         const typename LS::store_t *__restrict__ Wj = W + (size_t)j * 9 * V;
         C chi[4][3];
@@ -751,7 +751,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
             }
 
     for (int k = q; k < Slabs<KIND>::n; k += NSPLIT) {
-        const int j = Slabs<KIND>::at(k, a.reverse);
+        const int j = Slabs<KIND>::at(k);
         const DirW<RT, DAG, KIND> dw(j);
         const typename LS::store_t *__restrict__ Wj = W + (size_t)j * 9 * V;
         C wl[3][3];
