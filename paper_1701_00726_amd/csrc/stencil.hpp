@@ -46,7 +46,7 @@ struct StencilArgs {
     int colz;     // column traversal depth in z (0 = lexicographic tiles)
     int coly;     // column traversal width in tile rows along y (>= 1)
     int xcd_remap;
-    bool reverse;  // walk the tiles from the last to the first (stencil_launch)
+    int reverse;  // walk the tiles from the last to the first (stencil_launch)
     int ncol;     // columns (right-hand sides); column c lives at offset c * 12 V
     int nslots;   // partial-sum slots per column the reductions read (one per tile,
                   // filled by the tile's block); a kernel with fewer blocks zeroes the slots it does
