@@ -278,20 +278,31 @@ static void line_columns(const Geom &g, int lines, int cap, StencilConfig &c) {
         }
 }
 
-// The four-right-hand-side kernel: blocks of exactly 48 sites in whole x-lines, groups of four right-hand
-// sides that are full, or in FP64 lack one (an empty place costs as much as a full one).  24^3x48: FP64 4
-// right-hand sides 3.75 -> 2.9 ms, 7: 6.7 -> 5.6, 12: 10.9 -> 8.5, 6 no gain; FP32 4: 2.33 -> 1.88, 12: 6.7 ->
-// 5.6, 7: 4.0 -> 3.7, 3 slower; bfloat16 links 12: 6.2 -> 5.6, 7 and 3 slower.  12^3x24, 4: FP64 248 -> 202
-// us, FP32 154 -> 140.  In FP32 it needs a block per CU and group (192 tiles, 12 right-hand sides 102
-// against 105 us).  Blocks with idle rows lose (20-site lines: FP32 650 against 1120 us), and so do lines of 16
-// and 32 sites, which the x-line and standard kernels fill (16^3x64, 12: FP64 3.6 against 3.7 ms).  The
-// kernel's 32-bit offsets reach over the 48 staged components.
+constexpr int CUS = 256;
+
+// The four-right-hand-side kernel: blocks of exactly 48 sites in whole x-lines, one block a CU, 50 us (FP32 and
+// bfloat16 links 35) however full the chip is: a last round of few blocks and groups with empty places cost as
+// much as full ones.  The sites and right-hand sides have to fill more than three quarters of its rounds in
+// FP64, five sixths in FP32.  Above the line, the better of line and cut tiles -> this kernel: FP64 24x20x12x6
+// x 4 (94% full) 187 -> 164 us, 12x4x6x20 x 7 (82%) 58 -> 54, 12x8x8x8 x 8 (100%) 66 -> 54; FP32 24x4x12x16 x 8
+// (100%) 126 -> 106, 12^3x24 x 4 (84%) 149 -> 139, bfloat16 links 48x16x4x12 x 4 (100%) 118 -> 105.  Below it:
+// FP64 24x4x8x8 x 4 (50%) 40 -> 51, 48x2x12x24 x 4 (75%) 142 -> 161, 24x8x12x18 x 3 (63%) 190 -> 202; FP32
+// 12x8x12x12 x 4 (56%) 61 -> 70, bfloat16 links 12x20x16x8 x 4 (83%) 84 -> 104.  24^3x48 x 12: FP64 10.9 -> 8.5
+// ms, FP32 6.7 -> 5.6.
+// Groups of four that are full, or in FP64 lack one (24^3x48 x 7: FP64 6.7 -> 5.6 ms, FP32 4.0 -> 3.7, bfloat16
+// links slower); beyond four rounds, where the other tiles slow down too, the empty place does not count
+// (24x24x18x28 x 3 1460 -> 1310 us).  Blocks with idle rows lose (20-site lines: FP32 650 against 1120 us), and
+// so do lines of 16 and 32 sites, which the x-line and standard kernels fill (16^3x64 x 12: FP64 3.6 against
+// 3.7 ms).  The kernel's 32-bit offsets reach over the 48 staged components.
 static bool rows_fit(const Geom &g, int prec, int ncol) {
     const int Lx = g.L[0];
     if (Lx != 12 && Lx != 24 && Lx != 48) return false;
     if (g.L[1] % (48 / Lx) || g.V > 0xffffffffLL / 48) return false;
-    if (prec == BRI_F64) return ncol >= 3 && (ncol % 4 == 0 || ncol % 4 == 3);
-    return ncol % 4 == 0 && g.V / 48 >= 256;
+    if (ncol % 4 && !(prec == BRI_F64 && ncol % 4 == 3)) return false;
+    if (prec != BRI_F64 && g.V / 48 < CUS) return false;
+    const long long tiles = g.V / 48, groups = (ncol + 3) / 4, rounds = (tiles * groups + CUS - 1) / CUS;
+    const long long work = tiles * (rounds > 4 ? 4 * groups : ncol);
+    return prec == BRI_F64 ? work > 3 * CUS * rounds : 3 * work > 10 * CUS * rounds;
 }
 
 bool forms_alpha(const StencilConfig &cfg, int ndots) {
