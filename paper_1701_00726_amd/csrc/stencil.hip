@@ -334,16 +334,17 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     }
     int n = 0;
     const bool fit = lines_fit(g, &n);
-    const int tiles = fit ? line_tiles(g, n) : g.V / 64;
-    // FP64, one right-hand side, up to 256 tiles: twelve waves on each (40 slabs in 4 turns instead of
-    // 10), 8x8x8x16 31 -> 22.5 us; at 12^4 (324 line tiles) four waves are faster (49 against 53 us).
-    const bool few = kind == KERN_BRI && prec == BRI_F64 && ncol == 1 && tiles <= 256;
+    const int tiles = fit ? line_tiles(g, n) : 0;
+    if (!fit) return;
+    // FP64, one right-hand side, at most half as many line tiles as CUs: twelve waves on each (40 slabs in 4
+    // turns instead of 10), 48x8x4x4 25.0 -> 21.9 us (four waves 23.5), 12x4x8x16 32 -> 21 (22.8); at 192 tiles
+    // slower than four (16x16x24x2 26.5 against 25.4), and on cut tiles throughout (2x6x32x12 35.9 against 33.3).
+    const bool few = kind == KERN_BRI && prec == BRI_F64 && ncol == 1 && tiles <= CUS / 2;
     if (few) {
         c.variant = VAR_STANDARD;
         c.rpt = 0;
         c.nsplit = 12;
     }
-    if (!fit) return;
     if (kind == KERN_BRI && ncol != 2 && xline_fits(g)) return;  // whole-line tiles already
     // Wilson: up to 2048 tiles of 16 x 4 stay (16^3x32 FP64 29.9 against 31.7 us, 16^4 FP32 9.7 against 10.4).
     // Batches stay on cut tiles with runs of four sites or more, whose lanes all work, unless the lines use nine
