@@ -1,5 +1,7 @@
 // Stencil launches: tile planning, default configurations, the dispatch to the per-variant
 // instantiations (stencil_<precision>_<kernel>.hip) and the bri_apply / wil_apply entry points.
+#include <algorithm>
+
 #include "stencil.hpp"
 
 namespace bri {
@@ -99,10 +101,10 @@ int stencil_slots(const Geom &g, const StencilConfig &cfg) {
 }
 
 // The solvers apply D and D^dag in turn.  Links larger than the 256 MiB last-level cache, but not by much,
-// are read by each in the order in which the other has pushed them out; with the adjoint walking the tiles
-// backwards each finds what the other read last.  16 iterations of the multi-shift CG: 16^4 (360 MiB) 3.26 ->
-// 3.20 ms, 12^3x32 (303) 3.30 -> 3.25; 24^2x12x16 (607) 5.89 -> 5.95, 32^3x64 5% slower, and below the
-// cache's size (12^3x24, 227) no difference.
+// are read by each in the order in which the other has pushed them out; with the adjoint walking tiles and
+// slabs backwards each finds what the other read last.  16 iterations of the multi-shift CG: 16^4 (360
+// MiB) 3.35 -> 3.23 ms, 12^3x32 (303) 3.34 -> 3.23; 24^2x12x16 (607) 5.89 -> 5.95, 32^3x64 5% slower, and
+// below the cache's size (12^3x24, 227) no difference.
 static bool reverse_pays(const Geom &g, int prec) {
     const long long bytes = 360LL * g.V * (prec == BRI_F64 ? 16 : prec == BRI_F32 ? 8 : 4);
     return bytes > 256LL << 20 && bytes <= 512LL << 20;
@@ -310,6 +312,78 @@ bool forms_alpha(const StencilConfig &cfg, int ndots) {
     return ndots <= MAX_DOTS && (cfg.small > 0 || cfg.rpt == 0);
 }
 
+// The blocks of a launch on `tiles` tiles, and how many of them the chip holds at once: two a CU in FP64
+// (registers), one with the sums of several right-hand sides per thread in LDS; in FP32 four (x-line) or five,
+// three, two and one with two, three and four per thread.
+static long long launch_blocks(long long tiles, int ncol, const StencilConfig &c) {
+    const int r = c.rpt > 1 ? c.rpt : 1;
+    return tiles * ((ncol + r - 1) / r);
+}
+static int resident_blocks(int prec, const StencilConfig &c) {
+    const int f32[5] = {c.variant == VAR_XLINE ? 4 : 5, 5, 3, 2, 1};
+    return CUS * (prec != BRI_F64 ? f32[c.rpt] : c.rpt > 1 ? 1 : 2);
+}
+
+// The launch on tiles of n whole x-lines that leave lanes idle against the one on the cut tiles (c), which have a
+// site on every lane: whether the cut tiles stay.  What decides is whether they hold whole x-lines too (4-, 8-
+// and 16-site lines stacked over y, z and t), and in how long runs of consecutive sites; below, cut -> line
+// tiles, one right-hand side where no number is given.
+static bool cut_stays(const Geom &g, int prec, int ncol, int kind, const StencilConfig &c, const StencilConfig &line) {
+    // (as plan_tile and the 16 x 4 columns choose them: powers of two up to 16, x first)
+    int run = 1;
+    bool whole = true;
+    for (int mu = 0, all = 1; mu < 4 && all; ++mu) {
+        const int pow2 = g.L[mu] & -g.L[mu], t = std::min({pow2, 16, 64 / run});
+        all = t == g.L[mu];
+        if (mu == 0) whole = all;
+        run *= t;
+    }
+    const long long cut = g.V / 64, tiles = line_tiles(g, line.lines);
+    const bool three_quarters = 4LL * g.V >= 3LL * 64 * tiles, most = 8LL * g.V >= 7LL * 64 * tiles,
+               nine_tenths = 10LL * g.V >= 9LL * 64 * tiles;
+    if (kind == KERN_WIL) {
+        // Batches on whole lines, or on runs of four sites or more unless the lines use nine lanes in ten as well
+        // (24^3x48 x 12: FP64 2.79 -> 3.27 ms; 12^3x24 x 3: FP32 21 -> 28 us; 20x12x28x24, 95%, 1.2 to 1.4
+        // times faster on lines); shorter runs gain 1.1 to 13 times (6x16x12x48 x 9 with bfloat16 links loses,
+        // 68 -> 80 us).
+        if (ncol > 1) return g.L[0] % 4 == 0 && (whole || !nine_tenths);
+        // One right-hand side, bound by HBM or latency: whole x-lines either way (2x40x14x28 FP32 6.4 -> 8.9 us,
+        // 8x20x20x32 bfloat16 links 8% slower), runs of 16 (48-site lines, 48x6x8x28 FP32 10.2 -> 12.8 us), and
+        // where a second block a CU starts (24x6x16x6 FP64 5.6 -> 6.6 us).  Shorter runs gain, 24^3x48 FP64
+        // 177 -> 168 us.
+        return (!most && (whole || run >= 16)) || (cut <= CUS && tiles > CUS);
+    }
+    // The cut tiles in one round of resident blocks and the line tiles in more: FP64 24x24x6x4 x 2 48 -> 60 us,
+    // 8x8x8x32 x 3 56 -> 63, bfloat16 links with idle lanes 48x2x24x6 x 4 49 -> 59.  (FP32 gains all the same,
+    // 64x20x2x16 x 2 1.3 times, and so do shorter runs.)
+    if (run >= 8 && (prec == BRI_F64 || (prec == BRI_F32_BF16W && ncol > 1 && !most)) &&
+        launch_blocks(cut, ncol, c) <= resident_blocks(prec, c) &&
+        launch_blocks(tiles, ncol, line) > resident_blocks(prec, line))
+        return true;
+    // Both whole lines, seven lanes in eight work (nine in ten for a batch of nine or more, 16x14x8x32 FP32 x 12
+    // 435 -> 497 us; 8x28x40x16 x 5 615 -> 539): only one right-hand side in FP64 up to 512 tiles, where the order
+    // of the tiles alone differs (16x24x18x2 24.6 -> 27.0 us).
+    if (whole && (ncol < 9 ? most : nine_tenths)) return prec == BRI_F64 && ncol == 1 && tiles <= 512;
+    // Both whole lines, the cut tiles' runs at least eight sites: the idle lanes cost (8x4x40x64 FP64 x 2 220 -> 343
+    // us, 4x8x40x14 bfloat16 links x 7 98 -> 146), except where
+    if (whole && run >= 8) {
+        if (ncol == 1 && prec != BRI_F32_BF16W) {
+            // - large lattices at one right-hand side gain the columns' order (8x28x28x28 FP64 1.21 times);
+            if (cut >= 512 && three_quarters) return false;
+            // - FP64 takes no further block a CU (4x18x32x8 54 -> 42 us; 4x8x20x24, one more, 25.0 -> 34.5);
+            if (prec == BRI_F64) return (tiles + CUS - 1) / CUS > (cut + CUS - 1) / CUS;
+            // - the runs are no longer (4x18x20x24 FP32 61 -> 46 us).
+            return run > 8;
+        }
+        // - a batch gets a block a CU or less (FP64 8x6x8x6 x 4 1.3 times), or is one of three, whose cut tiles
+        //   carry all three per thread (4x12x28x6 61 -> 43 us);
+        if (prec == BRI_F64 && (launch_blocks(tiles, ncol, line) <= CUS || (ncol == 3 && three_quarters))) return false;
+        // - the runs are no longer and few lanes idle (4x14x14x64 bfloat16 links x 8 1.3 times).
+        return run > 8 || !three_quarters;
+    }
+    return false;
+}
+
 // Replaces the tile configuration by the small-lattice kernel or whole-line tiles where they measured
 // faster.
 static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilConfig &c) {
@@ -332,67 +406,64 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
         line_columns(g, c.rows, 36, c);
         return;
     }
-    int n = 0;
-    const bool fit = lines_fit(g, &n);
-    const int tiles = fit ? line_tiles(g, n) : 0;
-    if (!fit) return;
-    // FP64, one right-hand side, at most half as many line tiles as CUs: twelve waves on each (40 slabs in 4
-    // turns instead of 10), 48x8x4x4 25.0 -> 21.9 us (four waves 23.5), 12x4x8x16 32 -> 21 (22.8); at 192 tiles
-    // slower than four (16x16x24x2 26.5 against 25.4), and on cut tiles throughout (2x6x32x12 35.9 against 33.3).
-    const bool few = kind == KERN_BRI && prec == BRI_F64 && ncol == 1 && tiles <= CUS / 2;
-    if (few) {
-        c.variant = VAR_STANDARD;
-        c.rpt = 0;
-        c.nsplit = 12;
-    }
-    if (kind == KERN_BRI && ncol != 2 && xline_fits(g)) return;  // whole-line tiles already
-    // Wilson: up to 2048 tiles of 16 x 4 stay (16^3x32 FP64 29.9 against 31.7 us, 16^4 FP32 9.7 against 10.4).
-    // Batches stay on cut tiles with runs of four sites or more, whose lanes all work, unless the lines use nine
-    // lanes in ten as well (24^3x48, 12: FP64 2.79 against 3.27 ms; 12^3x24, 3: FP32 21 against 28 us;
-    // 20x12x28x24, 95%, 1.2 to 1.4 times faster on lines; 10-, 18- and 31-site lines 1.3 to 13 times)
-    if (kind == KERN_WIL && ((c.colz > 0 && g.V / 64 <= 2048) ||
-                             (ncol > 1 && g.L[0] % 4 == 0 && 9LL * 64 * tiles > 10LL * g.V)))
-        return;
-    // (16 x 4 tiles in columns one row wide: 16^4 overlap apply 4.02 ms, 4.15 in columns of 4 rows; the
-    // gradient's batches of 2 and 32 likewise, 13.3 against 13.5 ms; 3 right-hand sides gain, 312 -> 280 us)
-    if (kind == KERN_BRI && ncol != 3 && prec == BRI_F64 && tiles <= 1024 && c.colz > 0 && !few) return;
-    c.lines = n;
-    c.xcd_remap = 1;
+    StencilConfig line = c;
+    if (!lines_fit(g, &line.lines)) return;
+    line.xcd_remap = 1;
+    const int tiles = line_tiles(g, line.lines);
     if (kind == KERN_WIL) {
+        // Up to 2048 tiles of 16 x 4 stay (16^3x32 FP64 29.9 against 31.7 us, 16^4 FP32 9.7 against 10.4).
+        if ((c.colz > 0 && g.V / 64 <= 2048) || cut_stays(g, prec, ncol, kind, c, line)) return;
         // the four one-hop slabs: 960 bytes of FP64 links and spinors a site, deep columns.  32^3x64
         // FP64 755 -> 496 us, FP32 393 -> 312; 24^3x48 FP64 177 -> 166
         if (ncol == 1) {
-            c.rpt = 0;
-            c.nsplit = g.V / 64 >= 8192 ? 2 : 4;
+            line.rpt = 0;
+            line.nsplit = g.V / 64 >= 8192 ? 2 : 4;
         }
-        line_columns(g, n, 64, c);
+        line_columns(g, line.lines, 64, line);
+        c = line;
         return;
     }
-    if (few) {
-        line_columns(g, n, 36, c);
+    if (ncol != 2 && xline_fits(g)) return;  // whole-line tiles already
+    line.rpt = 0;
+    if (prec == BRI_F64 && ncol == 1 && tiles <= CUS / 2) {
+        // at most half as many tiles as CUs: twelve waves on each (40 slabs in 4 turns instead of 10), 48x8x4x4
+        // 25.0 -> 21.9 us (four waves 23.5), 12x4x8x16 32 -> 21 (22.8); at 192 tiles slower than four
+        // (16x16x24x2 26.5 against 25.4), and on cut tiles throughout (2x6x32x12 35.9 against 33.3)
+        line.variant = VAR_STANDARD;
+        line.nsplit = 12;
+        line_columns(g, line.lines, 36, line);
+        c = line;
         return;
     }
+    // Pairs of right-hand sides pay where at most one place in six is empty: on more than 1024 tiles in FP64 they
+    // are level with one per thread for 5, 5% faster for 7 and 12% slower for 3.
+    const int pairs = (ncol + 1) / 2;
+    const bool paired = ncol > 1 && 6 * ncol >= 10 * pairs;
+    // (16 x 4 tiles in columns one row wide: 16^4 overlap apply 4.02 ms, 4.15 in columns of 4 rows; the
+    // gradient's batches of 2 and 32 likewise, 13.3 against 13.5 ms; 3 right-hand sides gain, 312 -> 280 us)
+    if (prec == BRI_F64 && tiles <= 1024 && c.colz > 0 && (ncol == 1 || paired)) return;
     // One right-hand side per thread on the x-line kernel, or two (FP64) or three per thread on the
     // standard kernel, which loads a link once for them but each neighbour spinor separately.  12
     // right-hand sides at 24^3x48: FP64 12.5 ms (x-line) against 11.0 (R = 2), FP32 6.92 against
     // 6.83 (R = 3); 3 right-hand sides at 20x12x28x24: FP64 705 us (x-line) against 772, FP32 374
     // against 424.  Below 256 blocks the wider launch wins: 8^4, 4 right-hand sides 35 against 44 us.
-    c.variant = VAR_XLINE;
-    c.rpt = 0;
-    c.nsplit = 4;
-    const long long pair_blocks = (long long)tiles * ((ncol + 1) / 2);
-    if (prec == BRI_F64 && ncol >= 2 && ncol != 3 && pair_blocks >= 256) {
-        c.variant = VAR_STANDARD;
-        c.rpt = 2;
+    line.variant = VAR_XLINE;
+    line.nsplit = 4;
+    const long long pair_blocks = (long long)tiles * pairs;
+    if (prec == BRI_F64 && paired && pair_blocks >= 256) {
+        line.variant = VAR_STANDARD;
+        line.rpt = 2;
     } else if (prec == BRI_F32 && ncol >= 9 && tiles >= 512) {
-        c.variant = VAR_STANDARD;
-        c.rpt = 3;
+        line.variant = VAR_STANDARD;
+        line.rpt = 3;
     } else if (prec == BRI_F64 && ncol == 1 && tiles <= 1024) {
         // up to a wave of blocks or two the shorter turns of the standard kernel (40 slabs in 10
         // against 27 groups in 7) balance better: 12^3x24 82 against 91 us, 16^4 125 against 130
-        c.variant = VAR_STANDARD;
+        line.variant = VAR_STANDARD;
     }
-    line_columns(g, n, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, c);
+    if (cut_stays(g, prec, ncol, kind, c, line)) return;
+    line_columns(g, line.lines, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, line);
+    c = line;
 }
 
 // Every launch leaves one pair of sums per tile; a tile holds at least 32 sites on average, 16 in the
