@@ -446,20 +446,26 @@ static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilCo
     // standard kernel, which loads a link once for them but each neighbour spinor separately.  12
     // right-hand sides at 24^3x48: FP64 12.5 ms (x-line) against 11.0 (R = 2), FP32 6.92 against
     // 6.83 (R = 3); 3 right-hand sides at 20x12x28x24: FP64 705 us (x-line) against 772, FP32 374
-    // against 424.  Below 256 blocks the wider launch wins: 8^4, 4 right-hand sides 35 against 44 us.
+    // against 424.
+    // Launches of up to a few rounds of blocks take the standard kernel with one per thread: the pairs' blocks are
+    // fewer and longer (FP64 up to 1024 blocks, 48x6x16x6 x 2 99 -> 85 us, 4x32x16x6 x 9 143 -> 124), and against
+    // the x-line kernel its turns are shorter, 40 slabs in 10 instead of 27 groups in 7 (FP64 up to 1024 tiles,
+    // 12^3x24 91 -> 82 us, 8x16x36x2 x 3 41 -> 38; FP32 up to 512 blocks, 16x40x4x12 33.3 -> 29.6, at 576 40.1
+    // against 43.9; bfloat16 links 8x24x12x12 32.1 -> 28.6).
     line.variant = VAR_XLINE;
     line.nsplit = 4;
-    const long long pair_blocks = (long long)tiles * pairs;
-    if (prec == BRI_F64 && paired && pair_blocks >= 256) {
+    if (prec == BRI_F64) {
+        if (paired && (long long)tiles * pairs >= 4 * CUS) {
+            line.variant = VAR_STANDARD;
+            line.rpt = 2;
+        } else if (tiles <= 4 * CUS) {
+            line.variant = VAR_STANDARD;
+        }
+    } else if ((long long)tiles * ncol <= 2 * CUS) {
         line.variant = VAR_STANDARD;
-        line.rpt = 2;
     } else if (prec == BRI_F32 && ncol >= 9 && tiles >= 512) {
         line.variant = VAR_STANDARD;
         line.rpt = 3;
-    } else if (prec == BRI_F64 && ncol == 1 && tiles <= 1024) {
-        // up to a wave of blocks or two the shorter turns of the standard kernel (40 slabs in 10
-        // against 27 groups in 7) balance better: 12^3x24 82 against 91 us, 16^4 125 against 130
-        line.variant = VAR_STANDARD;
     }
     if (cut_stays(g, prec, ncol, kind, c, line)) return;
     line_columns(g, line.lines, ncol > 1 ? 16 : prec == BRI_F64 ? 36 : 72, line);
