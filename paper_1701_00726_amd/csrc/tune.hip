@@ -60,6 +60,11 @@ static bri_stencil_cfg to_public(const StencilConfig &s) {
     return c;
 }
 
+// one right-hand side per thread on 1, 2 or 4 waves a tile (the t-streaming kernel ignores nsplit)
+static bool split_ok(const StencilConfig &c) {
+    return c.variant == VAR_TSTREAM || c.rpt != 0 || c.nsplit == 1 || c.nsplit == 2 || c.nsplit == 4;
+}
+
 static int time_config(const Geom &g, const void *W, int prec, const void *in, void *out, int ncol,
                        const StencilConfig &cfg, int reps, hipStream_t st, double *us) {
     StencilArgs a{};
@@ -183,7 +188,7 @@ int bri_stencil_time(const bri_geom *geom, const void *W, int prec, const void *
     if (!W || !in || !out || !us_per_launch || nrhs < 1 || reps < 1 || g.V % 64) return BRI_EINVAL;
     if (prec != BRI_F64 && prec != BRI_F32 && prec != BRI_F32_BF16W) return BRI_EINVAL;
     const StencilConfig c = cfg ? from_public(*cfg) : default_config(g, prec, nrhs);
-    if (c.rpt == 0 && nrhs > 65535) return BRI_EINVAL;
+    if ((c.rpt == 0 && nrhs > 65535) || (cfg && !split_ok(c))) return BRI_EINVAL;
     return time_config(g, W, prec, in, out, nrhs, c, reps, (hipStream_t)stream, us_per_launch);
 }
 
@@ -243,9 +248,7 @@ int bri_set_stencil_cfg(const bri_geom *geom, int prec, int nrhs, const bri_sten
     int tile[4], nb[4];
     if (plan_tile(g, c, tile, nb) != BRI_OK) return BRI_EINVAL;
     if (c.variant < VAR_STANDARD || c.variant > VAR_MFMA) return BRI_EINVAL;
-    if (c.rpt < 0 || c.rpt > 4 || (c.variant != VAR_TSTREAM && c.rpt == 0 && c.nsplit != 1 && c.nsplit != 2 &&
-                                   c.nsplit != 4))
-        return BRI_EINVAL;
+    if (c.rpt < 0 || c.rpt > 4 || !split_ok(c)) return BRI_EINVAL;
     g_tuned[key_of(g, prec, nrhs)] = c;
     return BRI_OK;
 }
