@@ -637,6 +637,9 @@ def main():
             # the 1-RHS launch over nc columns: a tile's columns run in consecutive blocks, so the
             # columns after the first find the tile's links in L2 and add mostly spinor traffic
             one = bri.get_stencil_cfg(L, bri.F64, 1)
+            if one.variant == bri.VARIANT_LIBRARY:  # not a launch that can be installed for nc columns
+                rec[f"cols_{nc}"] = {"skipped": "the 1-RHS default of this lattice is the library's own"}
+                continue
             xc = b12[:nc].clone()
             yc = torch.empty_like(xc)
             bri.set_stencil_cfg(L, bri.F64, nc, one)

@@ -368,7 +368,13 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
  *   3  matrix cores (BRI_F32 and BRI_F32_BF16W only): rpt = 1..4 right-hand sides
  *      per thread, the colour transport by FP32 MFMA (16 sites per wave, a site's
  *      four spins in four lanes), the spin weights applied across those lanes.
+ *   4  (BRI_VARIANT_LIBRARY) the library's own default where the fields cannot express it:
+ *      whole x-lines that leave lanes idle, twelve waves a tile, blocks of 16 or 48
+ *      sites.  bri_get_stencil_cfg and bri_autotune return it; every call that takes a
+ *      configuration reads it as that default and ignores the other fields, which hold the
+ *      64-site tiles that the default replaces.
  */
+#define BRI_VARIANT_LIBRARY 4
 typedef struct {
     int tile_x, tile_y, tile_z, tile_t;
     int col_z;
@@ -387,18 +393,17 @@ int bri_stencil_time(const bri_geom *geom, const void *W, int prec, const void *
                      const bri_stencil_cfg *cfg, int reps, double *us_per_launch, void *stream);
 
 /* bri_autotune -- times every candidate configuration for (geom, prec, nrhs)
- * as bri_stencil_time does, and the default, and installs the fastest in a process-wide table (none if
- * the default is the fastest; best is then what bri_get_stencil_cfg gives)
- * used by the Brillouin stencils (bri_apply, bri_apply_dag and the overlap solvers on the
+ * as bri_stencil_time does, and the default, and installs the fastest in a process-wide table (no
+ * entry if the default is the fastest; best is what bri_get_stencil_cfg then gives) used by the Brillouin stencils (bri_apply, bri_apply_dag and the overlap solvers on the
  * Brillouin kernel) for that lattice, precision and column count; the Wilson stencil keeps
  * the default configuration.  best / best_us may be NULL. */
 int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, void *out, int nrhs, int reps,
                  bri_stencil_cfg *best, double *best_us, void *stream);
 
-/* bri_set_stencil_cfg -- installs cfg for (geom, prec, nrhs); cfg = NULL removes
- * the entry.  bri_get_stencil_cfg -- the installed configuration, or the default one in the terms
- * of bri_stencil_cfg (64-site tiles; without an entry, launches on lattices whose x-lines do not fill
- * 64 lanes, and on fewer than 257 tiles, use tiles and wave counts that the struct cannot express). */
+/* bri_set_stencil_cfg -- installs cfg for (geom, prec, nrhs); cfg = NULL, or of variant
+ * BRI_VARIANT_LIBRARY, removes the entry.  bri_get_stencil_cfg -- the configuration that launches
+ * use: the installed one, or the default (of variant BRI_VARIANT_LIBRARY where the fields cannot
+ * express it), so that installing what it returned leaves the launches as they are. */
 int bri_set_stencil_cfg(const bri_geom *geom, int prec, int nrhs, const bri_stencil_cfg *cfg);
 int bri_get_stencil_cfg(const bri_geom *geom, int prec, int nrhs, bri_stencil_cfg *cfg);
 

@@ -33,6 +33,7 @@ F64, F32, F32_BF16W = 0, 1, 2
 KL_DIAG, KL_UPPER = 0, 1
 RELAX_OFF, RELAX_OMEGA, RELAX_BOUND = 0, 1, 2
 KERNEL_BRILLOUIN, KERNEL_WILSON = 0, 1
+VARIANT_LIBRARY = 4  # StencilCfg.variant: the default of the library, not expressible in the other fields
 OK, EINVAL, ENOCONV, ENAN, EHIP, ESCRATCH = 0, -1, -2, -3, -4, -5
 MAX_SHIFTS = 32
 STATUS_NAMES = {OK: "BRI_OK", EINVAL: "BRI_EINVAL", ENOCONV: "BRI_ENOCONV", ENAN: "BRI_ENAN", EHIP: "BRI_EHIP",
@@ -634,6 +635,8 @@ def autotune(L, W, prec, psi, reps=5, stream=None):
 
 
 def get_stencil_cfg(L, prec, nrhs):
+    """The configuration launches use; variant VARIANT_LIBRARY stands for a default that the other fields
+    cannot express."""
     cfg = StencilCfg()
     g = _geom(L)
     _check("bri_get_stencil_cfg", load().bri_get_stencil_cfg(ctypes.byref(g), int(prec), int(nrhs), ctypes.byref(cfg)))

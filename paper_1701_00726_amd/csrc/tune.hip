@@ -60,6 +60,14 @@ static bri_stencil_cfg to_public(const StencilConfig &s) {
     return c;
 }
 
+// the configuration of launches without an entry, as bri_stencil_cfg gives it
+static bri_stencil_cfg library_config(const Geom &g, int prec, int ncol) {
+    bri_stencil_cfg p = to_public(tile_config(g, prec, ncol, KERN_BRI));
+    const StencilConfig c = untuned_config(g, prec, ncol, KERN_BRI);
+    if (c.lines > 0 || c.small > 0 || c.rows > 0 || c.nsplit > 4) p.variant = BRI_VARIANT_LIBRARY;
+    return p;
+}
+
 // one right-hand side per thread on 1, 2 or 4 waves a tile (the t-streaming kernel ignores nsplit)
 static bool split_ok(const StencilConfig &c) {
     return c.variant == VAR_TSTREAM || c.rpt != 0 || c.nsplit == 1 || c.nsplit == 2 || c.nsplit == 4;
@@ -187,7 +195,11 @@ int bri_stencil_time(const bri_geom *geom, const void *W, int prec, const void *
     if (rc != BRI_OK) return rc;
     if (!W || !in || !out || !us_per_launch || nrhs < 1 || reps < 1 || g.V % 64) return BRI_EINVAL;
     if (prec != BRI_F64 && prec != BRI_F32 && prec != BRI_F32_BF16W) return BRI_EINVAL;
-    const StencilConfig c = cfg ? from_public(*cfg) : default_config(g, prec, nrhs);
+    const bool library = cfg && cfg->variant == BRI_VARIANT_LIBRARY;
+    const StencilConfig c = library ? untuned_config(g, prec, nrhs, KERN_BRI)
+                            : cfg   ? from_public(*cfg)
+                                    : default_config(g, prec, nrhs);
+    if (library) cfg = nullptr;  // nothing of it to check
     if ((c.rpt == 0 && nrhs > 65535) || (cfg && !split_ok(c))) return BRI_EINVAL;
     return time_config(g, W, prec, in, out, nrhs, c, reps, (hipStream_t)stream, us_per_launch);
 }
@@ -200,9 +212,9 @@ int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, 
     if (rc != BRI_OK) return rc;
     if (!W || !in || !out || nrhs < 1 || reps < 1 || g.V % 64) return BRI_EINVAL;
     if (prec != BRI_F64 && prec != BRI_F32 && prec != BRI_F32_BF16W) return BRI_EINVAL;
-    // the default first: it may be a whole-line launch that bri_stencil_cfg cannot express, and stays
-    // (nothing installed) if no candidate beats it
-    StencilConfig bc = tile_config(g, prec, nrhs, KERN_BRI);
+    // the default first: it may be a launch that bri_stencil_cfg cannot express, and stays (nothing installed) if
+    // no candidate beats it
+    StencilConfig bc;
     double bus = 0.0;
     rc = time_config(g, W, prec, in, out, nrhs, untuned_config(g, prec, nrhs, KERN_BRI), reps, (hipStream_t)stream, &bus);
     if (rc == BRI_EINVAL) bus = 1e300;
@@ -228,7 +240,7 @@ int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, 
         else
             g_tuned[key_of(g, prec, nrhs)] = bc;
     }
-    if (best) *best = to_public(bc);
+    if (best) *best = keep ? library_config(g, prec, nrhs) : to_public(bc);
     if (best_us) *best_us = bus;
     return BRI_OK;
 }
@@ -240,7 +252,7 @@ int bri_set_stencil_cfg(const bri_geom *geom, int prec, int nrhs, const bri_sten
     if (rc != BRI_OK) return rc;
     if (nrhs < 1) return BRI_EINVAL;
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    if (!cfg) {
+    if (!cfg || cfg->variant == BRI_VARIANT_LIBRARY) {
         g_tuned.erase(key_of(g, prec, nrhs));
         return BRI_OK;
     }
@@ -260,8 +272,7 @@ int bri_get_stencil_cfg(const bri_geom *geom, int prec, int nrhs, bri_stencil_cf
     if (rc != BRI_OK) return rc;
     if (!cfg || nrhs < 1) return BRI_EINVAL;
     StencilConfig c;
-    if (!tuned_config(g, prec, nrhs, &c)) c = tile_config(g, prec, nrhs, KERN_BRI);
-    *cfg = to_public(c);
+    *cfg = tuned_config(g, prec, nrhs, &c) ? to_public(c) : library_config(g, prec, nrhs);
     return BRI_OK;
 }
 
