@@ -31,6 +31,7 @@
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <map>
 #include <vector>
 
 #include "common.hpp"
@@ -197,18 +198,37 @@ struct Level {
 };
 constexpr int NVEC = 7;
 
-// the pinned host memory that the partial sums of one solve go to
+// The pinned host memory that the partial sums of a solve go to: one buffer (256 KiB) per host thread and device,
+// allocated on the thread's first solve there and freed when the thread ends, so that no solve pins or frees
+// memory on its path (50 us a solve, and freeing waits for the whole device).  A thread runs one solve at a time.
+constexpr size_t SUMS_COUNT = (size_t)MAXD * STEP_BLOCKS * MAXC;
+struct ThreadSums {
+    std::map<int, double2 *> bufs;
+    ~ThreadSums() {
+        for (auto &b : bufs) (void)hipHostFree(b.second);
+    }
+    double2 *get(int dev) {
+        auto it = bufs.find(dev);
+        if (it != bufs.end()) return it->second;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, SUMS_COUNT * sizeof(double2), hipHostMallocDefault) != hipSuccess) return nullptr;
+        return bufs[dev] = (double2 *)p;
+    }
+};
+static thread_local ThreadSums t_sums;
+
 struct HostSums {
     double2 *p = nullptr;
     hipStream_t s = nullptr;
-    bool get(size_t count, hipStream_t stream) {
+    int dev = 0;
+    bool get(hipStream_t stream) {
         s = stream;
-        return hipHostMalloc((void **)&p, count * sizeof(double2), hipHostMallocDefault) == hipSuccess;
+        if (hipGetDevice(&dev) == hipSuccess) p = t_sums.get(dev);
+        return p != nullptr;
     }
     ~HostSums() {
-        if (!p) return;
-        (void)hipStreamSynchronize(s);  // a launch of a solve that failed may still write
-        (void)hipHostFree(p);
+        // a launch of a solve that failed may still write; if that cannot be waited for, the buffer is given up
+        if (p && hipStreamSynchronize(s) != hipSuccess) t_sums.bufs.erase(dev);
     }
 };
 
@@ -597,7 +617,7 @@ int ov_solve(const bri_geom *geom, const void *W64, const void *Wlo, const ov_pa
     c.n = (size_t)12 * g.V;
     c.ncol = nrhs;
     c.s = (hipStream_t)stream;
-    if (!c.sums.get((size_t)MAXD * STEP_BLOCKS * nrhs, c.s)) return BRI_EHIP;
+    if (!c.sums.get(c.s)) return BRI_EHIP;
     char *base = (char *)work;
     auto take = [&](size_t b) {
         char *p = base;
