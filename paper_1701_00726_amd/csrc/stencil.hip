@@ -289,8 +289,7 @@ constexpr int CUS = 256;
 // x 4 (94% full) 187 -> 164 us, 12x4x6x20 x 7 (82%) 58 -> 54, 12x8x8x8 x 8 (100%) 66 -> 54; FP32 24x4x12x16 x 8
 // (100%) 126 -> 106, 12^3x24 x 4 (84%) 149 -> 139, bfloat16 links 48x16x4x12 x 4 (100%) 118 -> 105.  Below it:
 // FP64 24x4x8x8 x 4 (50%) 40 -> 51, 48x2x12x24 x 4 (75%) 142 -> 161, 24x8x12x18 x 3 (63%) 190 -> 202; FP32
-// 12x8x12x12 x 4 (56%) 61 -> 70, bfloat16 links 12x20x16x8 x 4 (83%) 84 -> 104.  24^3x48 x 12: FP64 10.9 -> 8.5
-// ms, FP32 6.7 -> 5.6.
+// 12x8x12x12 x 4 (56%) 61 -> 70, bfloat16 links 12x20x16x8 x 4 (83%) 84 -> 104.
 // Groups of four that are full, or in FP64 lack one (24^3x48 x 7: FP64 6.7 -> 5.6 ms, FP32 4.0 -> 3.7, bfloat16
 // links slower); beyond four rounds, where the other tiles slow down too, the empty place does not count
 // (24x24x18x28 x 3 1460 -> 1310 us).  Blocks with idle rows lose (20-site lines: FP32 650 against 1120 us), and
@@ -388,8 +387,8 @@ static bool cut_stays(const Geom &g, int prec, int ncol, int kind, const Stencil
 // faster.
 static void lines_default(const Geom &g, int prec, int ncol, int kind, StencilConfig &c) {
     // Up to about a block per CU (two in FP64 batches, six in FP32 and with bfloat16 links) of the small-
-    // lattice kernel, eight waves each up to 256 blocks: 8^4 FP64 21.6 -> 15.5 us, FP32 16.7 -> 7.1,
-    // bfloat16 links 14.3 -> 6.8; 4^4 x 6 FP64 33.5 -> 9.6.  Beyond, its blocks queue and the tile
+    // lattice kernel, eight waves each up to 256 blocks: 8^4 FP64 21.6 -> 10.6 us, FP32 16.7 -> 6.9,
+    // bfloat16 links 14.3 -> 6.8; 4^4 x 4 FP64 33.7 -> 8.0.  Beyond, its blocks queue and the tile
     // kernels' shared loads win: FP64 8x8x8x16 24.0 against 22.5 us, 8^4 x 3 35 against 29; FP32
     // 8x8x8x16 x 6 51 against 39, 12^4 x 2 48 against 46.
     const long long blocks16 = (long long)g.V / 16 * ncol;

@@ -27,7 +27,8 @@ __device__ __forceinline__ void axpy_ic(C &acc, R a, const C &v) {
     acc.y = fma(a, v.x, acc.y);
 }
 
-// acc[s][c] += (a + sum_mu cmu gamma_mu) chi[s][c];  branches are wave-uniform.
+// acc[s][c] += (a + sum_mu cmu gamma_mu) chi[s][c];  a zero weight adds nothing (0 * inf would be NaN).  The
+// branches are wave-uniform but in the small-lattice kernel.
 template <typename C, typename R>
 __device__ __forceinline__ void spin_accumulate(C (&acc)[4][3], const C (&chi)[4][3], R a, R c0, R c1, R c2, R c3) {
 #pragma unroll

@@ -24,9 +24,9 @@
 // keeps three sums of its own spin (unchanged, to be sent to spin 3 - s, to spin s ^ 2) and the spins
 // are exchanged once, after the last group.
 //
-// What holds it now is the latency of a group (LDS about half busy, vector issue 57%).  24^3x48, 12
-// right-hand sides: FP64 11.4 -> 8.9 ms, FP32 6.9 -> 5.8 (reading when used: 6.6), bfloat16 links 6.65 ->
-// 5.7; FP64 with the operands a group ahead spills and takes 35 ms.
+// What holds it is the latency of a group, from barrier to barrier.  24^3x48, 12 right-hand sides, line tiles ->
+// here: FP64 11.0 -> 8.7 ms, FP32 6.8 -> 5.7 (reading when used: 6.6), bfloat16 links 6.2 -> 5.65; FP64 with the
+// operands a group ahead spills and takes 35 ms.
 #pragma once
 
 #include "stencil_core.hpp"
@@ -221,10 +221,13 @@ void stencil_rows_kernel(StencilArgs a) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) pc[c] = buf[pbase + c * PITCH + m0];
     };
-    // Group g of this kind, the next one of kind knext.  The barriers around the scheduler keep the LDS
-    // reads and the staging where they are written: hoisted, their registers spill.
-    auto step = [&](auto kind, auto knext, auto set, int g) {
-        constexpr int K = decltype(kind)::value;
+    // Group g of this kind, the next one of kind knext; flat: d_z = d_t = 0.  A weight that is zero adds nothing, or
+    // an infinite neighbour would reach spins that its displacement does not couple (0 * inf): flat groups have
+    // no F2 terms, and those of d_y = 0 skip the one of F3 (a branch a term: FP64 8% slower, FP32 4%).  The
+    // barriers around the scheduler keep the LDS reads and the staging where they are written: hoisted, their
+    // registers spill.
+    auto step = [&](auto kind, auto knext, auto set, auto flat, int g) {
+        constexpr int K = decltype(kind)::value, FLAT = decltype(flat)::value;
         C *const cur = lds + (g & 1) * BUF, *const next = lds + ((g + 1) & 1) * BUF;
         if constexpr (!AHEAD) {
             __syncthreads();  // group g is staged, and every wave is done with the other buffer
@@ -270,6 +273,7 @@ void stencil_rows_kernel(StencilArgs a) {
         }
         if constexpr (K != 2) {
             const R cy = cm * (R)dy * g2, cz = cm * (R)dz * g3, ct = cm * (R)dt;
+            C vy[3];
             row_transport<K == 1>(u, wc, pc);
             if constexpr (AHEAD) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -280,9 +284,15 @@ void stencil_rows_kernel(StencilArgs a) {
             for (int c = 0; c < 3; ++c) {
                 const C v = cmake<C>(fma((R)-0.25, s[c].x, u[c].x), fma((R)-0.25, s[c].y, u[c].y));
                 axpy_c(A0[c], am, u[c]);
-                axpy_c(F3[c], cy, v);
-                axpy_c(F2[c], ct, v);
-                axpy_ic(F2[c], cz, v);
+                if constexpr (FLAT == 0) {
+                    axpy_c(F2[c], ct, v);
+                    axpy_ic(F2[c], cz, v);
+                }
+                vy[c] = v;
+            }
+            if (dy) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) axpy_c(F3[c], cy, vy[c]);
             }
         } else {
             const R diag = (R)a.diag;
@@ -303,6 +313,8 @@ void stencil_rows_kernel(StencilArgs a) {
     using Centre = std::integral_constant<int, 2>;
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, SETS - 1>;
+    using Deep = std::integral_constant<int, 0>;
+    using Flat = std::integral_constant<int, 1>;
     load(Even{}, 0);
     if constexpr (AHEAD) {
         load(Odd{}, 1);
@@ -316,25 +328,27 @@ void stencil_rows_kernel(StencilArgs a) {
         read_c(Own{}, lds);
 #pragma unroll 1
         for (int g = 0; g < 12; g += 2) {
-            step(Own{}, Own{}, Even{}, g);
-            step(Own{}, Own{}, Odd{}, g + 1);
+            step(Own{}, Own{}, Even{}, Deep{}, g);
+            step(Own{}, Own{}, Odd{}, Deep{}, g + 1);
         }
-        step(Own{}, Centre{}, Even{}, 12);
-        step(Centre{}, Partner{}, Odd{}, 13);
+        step(Own{}, Centre{}, Even{}, Flat{}, 12);
+        step(Centre{}, Partner{}, Odd{}, Flat{}, 13);
+        step(Partner{}, Partner{}, Even{}, Flat{}, 14);
 #pragma unroll 1
-        for (int g = 14; g < 26; g += 2) {
-            step(Partner{}, Partner{}, Even{}, g);
-            step(Partner{}, Partner{}, Odd{}, g + 1);
+        for (int g = 15; g < 27; g += 2) {  // (the reads of a next group after the last are unused)
+            step(Partner{}, Partner{}, Odd{}, Deep{}, g);
+            step(Partner{}, Partner{}, Even{}, Deep{}, g + 1);
         }
-        step(Partner{}, Partner{}, Even{}, 26);  // (the reads of a next group are unused)
     } else {
         stage(Even{}, lds);
         load(Even{}, 1);
 #pragma unroll 1
-        for (int g = 0; g < 13; ++g) step(Own{}, Own{}, Even{}, g);
-        step(Centre{}, Partner{}, Even{}, 13);
+        for (int g = 0; g < 12; ++g) step(Own{}, Own{}, Even{}, Deep{}, g);
+        step(Own{}, Centre{}, Even{}, Flat{}, 12);
+        step(Centre{}, Partner{}, Even{}, Flat{}, 13);
+        step(Partner{}, Partner{}, Even{}, Flat{}, 14);
 #pragma unroll 1
-        for (int g = 14; g < 27; ++g) step(Partner{}, Partner{}, Even{}, g);
+        for (int g = 15; g < 27; ++g) step(Partner{}, Partner{}, Even{}, Deep{}, g);
     }
 
     // the spin exchange, then the results through LDS into the staging's (component, site) order, in the

@@ -4,11 +4,12 @@
 // one right-hand side, a wave holds them four times over, and each of the 4 * NW groups of 16 lanes takes
 // its own stored slabs (40 / 32 = one or two per group with NW = 8 waves).  The slab index, and with it
 // the neighbours and spin weights, then differ between the groups of a wave, so the weights sit in
-// vector registers and every gamma term is applied, zero or not.  All 42 loads of a slab (both terms)
-// are requested before the first is used; FP64 takes 250 VGPRs for it, two waves per SIMD, no spills.
-// The partial sums of all groups meet in LDS; thread c * 16 + l finishes component c of site l.
-// Bound by that latency: 8^4 FP64 15.5 us (25.2 MB: 1.6 TB/s) against 21.6 with twelve waves on 64-site
-// tiles, FP32 7.1 against 16.7 us.
+// vector registers and a gamma term is applied to the lanes whose weight is not zero.  All 42 loads of a
+// slab (both terms) are requested before the first is used; FP64 takes 254 VGPRs for it, two waves per
+// SIMD, no spills.  The partial sums of all groups meet in LDS; thread c * 16 + l finishes component c of
+// site l.  Bound by that latency, two turns of it with eight waves, three with four: 8^4 FP64 10.6 us
+// (25.2 MB: 2.4 TB/s; 15.3 with every gamma term on every lane) against 21.6 with twelve waves on 64-site
+// tiles, FP32 6.9 against 16.7 us.
 #pragma once
 
 #include "stencil_core.hpp"
@@ -30,32 +31,6 @@ __device__ __forceinline__ void load_spinor(C (&p)[4][3], const C *__restrict__ 
     for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int b = 0; b < 3; ++b) p[s][b] = ps[(size_t)(s * 3 + b) * V + ys];
-}
-
-// acc += (a + sum_mu cmu gamma_mu) chi with per-lane weights
-template <typename C, typename R>
-__device__ __forceinline__ void spin_accumulate_all(C (&acc)[4][3], const C (&chi)[4][3], R a, R c0, R c1, R c2, R c3) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) axpy_c(acc[s][c], a, chi[s][c]);
-        axpy_ic(acc[0][c], -c0, chi[3][c]);  // gamma_1
-        axpy_ic(acc[1][c], -c0, chi[2][c]);
-        axpy_ic(acc[2][c], c0, chi[1][c]);
-        axpy_ic(acc[3][c], c0, chi[0][c]);
-        axpy_c(acc[0][c], -c1, chi[3][c]);  // gamma_2
-        axpy_c(acc[1][c], c1, chi[2][c]);
-        axpy_c(acc[2][c], c1, chi[1][c]);
-        axpy_c(acc[3][c], -c1, chi[0][c]);
-        axpy_ic(acc[0][c], -c2, chi[2][c]);  // gamma_3
-        axpy_ic(acc[1][c], c2, chi[3][c]);
-        axpy_ic(acc[2][c], c2, chi[0][c]);
-        axpy_ic(acc[3][c], -c2, chi[1][c]);
-        axpy_c(acc[0][c], c3, chi[2][c]);  // gamma_4
-        axpy_c(acc[1][c], c3, chi[3][c]);
-        axpy_c(acc[2][c], c3, chi[0][c]);
-        axpy_c(acc[3][c], c3, chi[1][c]);
-    }
 }
 
 template <class LS, int NW, bool DAG, int MODE>
@@ -107,9 +82,9 @@ __global__ __launch_bounds__(64 * NW) void stencil_small_kernel(StencilArgs a) {
         const R aw = scale_pow2((R)-0.125, -h), cw = scale_pow2((R)((DAG ? -16.0 : 16.0) / 27.0), -2 * h);
         const R c0 = cw * (R)d0, c1 = cw * (R)d1, c2 = cw * (R)d2, c3 = cw * (R)d3;
         transport_vals<C, R, false>(chi, wo, po);
-        spin_accumulate_all(acc, chi, aw, c0, c1, c2, c3);
+        spin_accumulate(acc, chi, aw, c0, c1, c2, c3);
         transport_vals<C, R, true>(chi, wp, pp);
-        spin_accumulate_all(acc, chi, aw, -c0, -c1, -c2, -c3);
+        spin_accumulate(acc, chi, aw, -c0, -c1, -c2, -c3);
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s)
