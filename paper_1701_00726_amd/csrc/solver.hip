@@ -350,7 +350,10 @@ __global__ __launch_bounds__(T) void ms_beta_kernel(ColState *states, const doub
                 if (i < ns)
 #pragma unroll
                     for (int l = 0; l < WIN; ++l) terms[i][l] = wgt * cw[l];
+                // the terms of the other lanes of this wave
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
                 double v = 0.0;
                 if (j <= m)
                     for (int k = i & 7; k < ns; k += 8) v += terms[k][j - 1];
