@@ -35,8 +35,7 @@ enum EpiMode {
     EPI_NORMS = 1,  // out = D in; partial sums of |out|^2 and |in|^2
     EPI_CG_R = 2,   // r -= alpha_c (D in + sigma0_c p); partial sums of |r|^2
     EPI_OV = 3,     // out = rho (b + D in)
-    EPI_SIGN = 4,   // out = gamma5 D in
-    EPI_RESID = 5   // out = b_{c mod b_mod} - (D in + sig_c xs); partial sums of |out|^2
+    EPI_SIGN = 4    // out = gamma5 D in
 };
 
 struct StencilArgs {
@@ -57,16 +56,14 @@ struct StencilArgs {
     double diag;  // kernel_diag(kind) + m0
     int kind;     // KernelKind
     // epilogue operands
-    double *partial;        // EPI_NORMS / EPI_CG_R / EPI_RESID: [ncol][nblk][2]
+    double *partial;        // EPI_NORMS / EPI_CG_R: [ncol][nblk][2]
     const void *p;          // EPI_CG_R
     void *r;                // EPI_CG_R
     const ColState *st;     // EPI_NORMS / EPI_CG_R: alpha, sigma0 and the done flag per column
     const double *dots;     // EPI_CG_R: [ncol][ndots][2], the partial sums |t|^2, |p|^2 from which each
-    int ndots;              // block forms alpha by itself; NULL: alpha is in st
-    const void *b;          // EPI_OV / EPI_RESID
-    int b_mod;              // EPI_RESID: column c uses b column (c % b_mod)
-    const void *xs;         // EPI_RESID
-    const double *sig;      // EPI_RESID: shift per column
+    int ndots;              // block forms alpha by itself (the scalar kernel forms it again, from the same
+                            // sums in another order: the two may differ in the last bit); NULL: alpha is in st
+    const void *b;          // EPI_OV
     double rho;             // EPI_OV
 };
 

@@ -79,14 +79,6 @@ __device__ __forceinline__ void epilogue(const StencilArgs &a, int col, int comp
     } else if constexpr (MODE == EPI_SIGN) {
         const R sg = comp < 6 ? (R)1 : (R)-1;  // gamma5 = diag(1, 1, -1, -1)
         ((C *)a.out)[idx] = cmake<C>(sg * v.x, sg * v.y);
-    } else if constexpr (MODE == EPI_RESID) {
-        const size_t bidx = ((size_t)(col % a.b_mod) * 12 + comp) * V + x;
-        const C b = ((const C *)a.b)[bidx];
-        const C xv = ((const C *)a.xs)[idx];
-        const R s = (R)a.sig[col];
-        const C o = cmake<C>(b.x - (v.x + s * xv.x), b.y - (v.y + s * xv.y));
-        ((C *)a.out)[idx] = o;
-        n0 += norm2(o);
     }
 }
 
@@ -252,7 +244,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_kernel(StencilArgs a) {
 #pragma unroll
     for (int i = 0; i < NCOMP; ++i)
         if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1, alpha);
-    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
         // deterministic: wave sums, then the NSPLIT wave totals in order
         n0 = wave_sum(n0);
         n1 = wave_sum(n1);
@@ -398,7 +390,7 @@ __global__ __launch_bounds__(64 * NSPLIT) void stencil_xline_kernel(StencilArgs 
 #pragma unroll
     for (int i = 0; i < NCOMP; ++i)
         if (site) epilogue<MODE, C, R>(a, col, q * NCOMP + i, x, V, res[i], n0, n1, alpha);
-    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
         n0 = wave_sum(n0);
         n1 = wave_sum(n1);
         if (lane == 0) {
@@ -532,7 +524,7 @@ __global__ __launch_bounds__(64 * MRHS_SPLIT) void stencil_xline_mrhs_kernel(Ste
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
             if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1, col_alpha<MODE>(a, col));
         }
-        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
             n0 = wave_sum(n0);
             n1 = wave_sum(n1);
             if (lane == 0) {
@@ -678,7 +670,7 @@ __global__ __launch_bounds__(STREAM_THREADS) void stencil_stream_kernel(StencilA
             for (int b = 0; b < 3; ++b) accp[sp][b] = accc[sp][b];
     }
 
-    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
         // deterministic: wave sums, then the wave totals in order; blocks fill slots
         // [0, gridDim.x) of the column and zero the rest of its nslots
         constexpr int NW = STREAM_THREADS / 64;
@@ -818,7 +810,7 @@ void stencil_mrhs_kernel(StencilArgs a) {
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, comp, x, V);
             if (site) epilogue<MODE, C, RT>(a, col, comp, x, V, v, n0, n1, col_alpha<MODE>(a, col));
         }
-        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
             // deterministic: wave sums, then the NSPLIT wave totals in order
             n0 = wave_sum(n0);
             n1 = wave_sum(n1);
@@ -877,7 +869,6 @@ inline hipError_t launch_1rhs(const StencilArgs &a, int mode, hipStream_t st) {
     case EPI_CG_R: hipLaunchKernelGGL((stencil_kernel<LS, NSPLIT, DAG, EPI_CG_R, KIND>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_kernel<LS, NSPLIT, DAG, EPI_OV, KIND>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_kernel<LS, NSPLIT, DAG, EPI_SIGN, KIND>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_kernel<LS, NSPLIT, DAG, EPI_RESID, KIND>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -893,7 +884,6 @@ inline hipError_t launch_mrhs(const StencilArgs &a, int mode, hipStream_t st) {
     case EPI_CG_R: hipLaunchKernelGGL((stencil_mrhs_kernel<LS, R, DAG, EPI_CG_R, KIND>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_mrhs_kernel<LS, R, DAG, EPI_OV, KIND>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_mrhs_kernel<LS, R, DAG, EPI_SIGN, KIND>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_mrhs_kernel<LS, R, DAG, EPI_RESID, KIND>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -908,7 +898,6 @@ inline hipError_t launch_stream(const StencilArgs &a, int mode, hipStream_t st) 
     case EPI_CG_R: hipLaunchKernelGGL((stencil_stream_kernel<LS, DAG, EPI_CG_R>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_stream_kernel<LS, DAG, EPI_OV>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_stream_kernel<LS, DAG, EPI_SIGN>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_stream_kernel<LS, DAG, EPI_RESID>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -923,7 +912,6 @@ inline hipError_t launch_xline(const StencilArgs &a, int mode, hipStream_t st) {
     case EPI_CG_R: hipLaunchKernelGGL((stencil_xline_kernel<LS, NSPLIT, DAG, EPI_CG_R>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_xline_kernel<LS, NSPLIT, DAG, EPI_OV>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_xline_kernel<LS, NSPLIT, DAG, EPI_SIGN>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_xline_kernel<LS, NSPLIT, DAG, EPI_RESID>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -939,7 +927,6 @@ inline hipError_t launch_xline_mrhs(const StencilArgs &a, int mode, hipStream_t 
     case EPI_CG_R: hipLaunchKernelGGL((stencil_xline_mrhs_kernel<LS, R, DAG, EPI_CG_R>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_xline_mrhs_kernel<LS, R, DAG, EPI_OV>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_xline_mrhs_kernel<LS, R, DAG, EPI_SIGN>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_xline_mrhs_kernel<LS, R, DAG, EPI_RESID>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -955,7 +942,6 @@ inline hipError_t launch_mfma(const StencilArgs &a, int mode, hipStream_t st) {
     case EPI_CG_R: hipLaunchKernelGGL((stencil_mfma_kernel<LS, R, DAG, EPI_CG_R>), grid, block, 0, st, a); break;
     case EPI_OV: hipLaunchKernelGGL((stencil_mfma_kernel<LS, R, DAG, EPI_OV>), grid, block, 0, st, a); break;
     case EPI_SIGN: hipLaunchKernelGGL((stencil_mfma_kernel<LS, R, DAG, EPI_SIGN>), grid, block, 0, st, a); break;
-    case EPI_RESID: hipLaunchKernelGGL((stencil_mfma_kernel<LS, R, DAG, EPI_RESID>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

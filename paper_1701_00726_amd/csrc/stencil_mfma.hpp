@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void stencil_mfma_kernel(StencilArgs a) {
                 clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)r * 12 * V, sub * 3 + b, x, V);
             epilogue<MODE, C, float>(a, col, sub * 3 + b, x, V, v, n0, n1, col_alpha<MODE>(a, col));
         }
-        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+        if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
             n0 = wave_sum(n0);
             n1 = wave_sum(n1);
             if (lane == 0) {

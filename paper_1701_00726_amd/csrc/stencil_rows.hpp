@@ -373,7 +373,7 @@ void stencil_rows_kernel(StencilArgs a) {
             clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in + (size_t)q * 12 * V, sc, own_site, (unsigned)V);
         epilogue<MODE, C, R>(a, col0 + q, sc, own_site, (unsigned)V, v, n0[q], n1[q], col_alpha<MODE>(a, col0 + q));
     }
-    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
         // deterministic: wave sums, then the wave totals in order
         __shared__ double wsum[ROWS_THREADS / 64][ROWS_RHS][2];
 #pragma unroll

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(64 * NW) void stencil_small_kernel(StencilArgs a) {
         if (a.g.csw != 0.0) clover_row<LS>(v, W + (size_t)LINK_SLAB_ENTRIES * V, in, comp, x, V);
         epilogue<MODE, C, R>(a, col, comp, x, V, v, n0, n1, alpha);
     }
-    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R || MODE == EPI_RESID) {
+    if constexpr (MODE == EPI_NORMS || MODE == EPI_CG_R) {
         // the twelve components sit in the first three waves; wave sums, then their totals in order
         __shared__ double wsum[3][2];
         n0 = wave_sum(n0);
