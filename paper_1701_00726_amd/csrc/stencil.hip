@@ -292,9 +292,10 @@ constexpr int CUS = 256;
 // 12x8x12x12 x 4 (56%) 61 -> 70, bfloat16 links 12x20x16x8 x 4 (83%) 84 -> 104.
 // Groups of four that are full, or in FP64 lack one (24^3x48 x 7: FP64 6.7 -> 5.6 ms, FP32 4.0 -> 3.7, bfloat16
 // links slower); beyond four rounds, where the other tiles slow down too, the empty place does not count
-// (24x24x18x28 x 3 1460 -> 1310 us).  Blocks with idle rows lose (20-site lines: FP32 650 against 1120 us), and
-// so do lines of 16 and 32 sites, which the x-line and standard kernels fill (16^3x64 x 12: FP64 3.6 against
-// 3.7 ms).  The kernel's 32-bit offsets reach over the 48 staged components.
+// (24x24x18x28 x 3 1460 -> 1310 us), nor in FP64's single round of more than 170 blocks (192: 24x8x4x12 x 3
+// 59 -> 51 us, 48x4x8x6 x 4 72 -> 52; 160: 24x4x10x4 x 8 45 -> 51).  Blocks with idle rows lose (20-site lines:
+// FP32 650 against 1120 us), and so do lines of 16 and 32 sites, which the x-line and standard kernels fill
+// (16^3x64 x 12: FP64 3.6 against 3.7 ms).  The kernel's 32-bit offsets reach over the 48 staged components.
 static bool rows_fit(const Geom &g, int prec, int ncol) {
     const int Lx = g.L[0];
     if (Lx != 12 && Lx != 24 && Lx != 48) return false;
@@ -302,6 +303,7 @@ static bool rows_fit(const Geom &g, int prec, int ncol) {
     if (ncol % 4 && !(prec == BRI_F64 && ncol % 4 == 3)) return false;
     if (prec != BRI_F64 && g.V / 48 < CUS) return false;
     const long long tiles = g.V / 48, groups = (ncol + 3) / 4, rounds = (tiles * groups + CUS - 1) / CUS;
+    if (rounds == 1 && prec == BRI_F64) return 3 * tiles * groups > 2 * CUS;
     const long long work = tiles * (rounds > 4 ? 4 * groups : ncol);
     return prec == BRI_F64 ? work > 3 * CUS * rounds : 3 * work > 10 * CUS * rounds;
 }
