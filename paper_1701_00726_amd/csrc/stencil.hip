@@ -346,7 +346,10 @@ static bool cut_stays(const Geom &g, int prec, int ncol, int kind, const Stencil
         // Batches on whole lines, or on runs of four sites or more unless the lines use nine lanes in ten as well
         // (24^3x48 x 12: FP64 2.79 -> 3.27 ms; 12^3x24 x 3: FP32 21 -> 28 us; 20x12x28x24, 95%, 1.2 to 1.4
         // times faster on lines); shorter runs gain 1.1 to 13 times (6x16x12x48 x 9 with bfloat16 links loses,
-        // 68 -> 80 us).
+        // 68 -> 80 us).  Two-site lines are whole either way: the cut tiles stay where they divide over the 8 XCDs
+        // (2x20x32x64 FP64 x 3 67 -> 95 us, 2x16x40x8 FP32 x 9 16 -> 30; else 2x50x48x12 bfloat16 links x 6 117 ->
+        // 53), and where they hold four lines or more in y and one lane in eight idles (2x40x28x14 x 8 30 -> 47).
+        if (ncol > 1 && g.L[0] == 2) return cut % 8 == 0 || (!most && g.L[1] % 4 == 0);
         if (ncol > 1) return g.L[0] % 4 == 0 && (whole || !nine_tenths);
         // One right-hand side, bound by HBM or latency: whole x-lines either way (2x40x14x28 FP32 6.4 -> 8.9 us,
         // 8x20x20x32 bfloat16 links 8% slower), runs of 16 (48-site lines, 48x6x8x28 FP32 10.2 -> 12.8 us), and
