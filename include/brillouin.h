@@ -394,8 +394,8 @@ int bri_stencil_time(const bri_geom *geom, const void *W, int prec, const void *
 
 /* bri_autotune -- times every candidate configuration for (geom, prec, nrhs)
  * as bri_stencil_time does, and the default, and installs the fastest in a process-wide table (no
- * entry if the default is the fastest; best is what bri_get_stencil_cfg then gives) used by the Brillouin stencils (bri_apply, bri_apply_dag and the overlap solvers on the
- * Brillouin kernel) for that lattice, precision and column count; the Wilson stencil keeps
+ * entry if the default is the fastest; best is what bri_get_stencil_cfg then gives) used by the
+ * Brillouin stencils (bri_apply, bri_apply_dag and the overlap solvers on the Brillouin kernel) for that lattice, precision and column count; the Wilson stencil keeps
  * the default configuration.  best / best_us may be NULL. */
 int bri_autotune(const bri_geom *geom, const void *W, int prec, const void *in, void *out, int nrhs, int reps,
                  bri_stencil_cfg *best, double *best_us, void *stream);
@@ -408,8 +408,8 @@ int bri_set_stencil_cfg(const bri_geom *geom, int prec, int nrhs, const bri_sten
 int bri_get_stencil_cfg(const bri_geom *geom, int prec, int nrhs, bri_stencil_cfg *cfg);
 
 /* bri_set_solver_graphs -- enable (1, the default) or disable (0) HIP-graph replay of
- * the multi-shift CG loop.  When enabled, each block of 8 iterations (six launches per
- * iteration) is captured once per solve layout (device, lattice, boundary condition, clover
+ * the multi-shift CG loop.  When enabled, each block of 8 iterations (four or five launches
+ * each) is captured once per solve layout (device, lattice, boundary condition, clover
  * switch, precision, kernel, mass, column count, workspace and link addresses, launch
  * configuration) on a library-owned stream and
  * replayed on the caller's stream; up to 16 instantiated graphs are cached per process and

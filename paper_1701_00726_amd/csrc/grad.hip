@@ -450,7 +450,7 @@ __global__ __launch_bounds__(128) void grad_level_kernel(Geom g, const double2 *
 // the displacements r +- e_mu; the mu of a site range follow each other on one XCD.  A single wave for all 27
 // left 2.5 waves a SIMD at 12^3x24; the loads in flight bound it (both steps' operands, 212 registers, two
 // waves a SIMD: fewer registers for three or four waves are slower): 332 -> 262 us there, 16^4 488 -> 413
-// (717 MB of G and W at 12^3x24: 163 us at the copy rate; G is read for up to four mu).
+// (717 MB of G and W at 12^3x24: 135 us at the 5.3 TB/s of a copy; G is read for up to four mu).
 constexpr int FORCE_WAVES = 3;
 __global__ __launch_bounds__(64 * FORCE_WAVES) void grad_force_kernel(Geom g, const double2 *__restrict__ U,
                                                                       const double2 *__restrict__ W,

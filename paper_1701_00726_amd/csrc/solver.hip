@@ -42,8 +42,8 @@
 // kernels; the host only polls a done flag every few iterations, and every
 // loop kernel returns at once for columns that are done.  Because no launch
 // argument changes between iterations, a block of iterations is captured once
-// into a HIP graph and replayed (one launch per block instead of six per
-// iteration); the instantiated graphs are cached per solve layout.
+// into a HIP graph and replayed (one launch per block instead of four or
+// five per iteration); the instantiated graphs are cached per solve layout.
 #include <math.h>
 
 #include <chrono>

@@ -88,3 +88,22 @@ def test_mixed_batch_24_48():
     _check(out[5], gg, f"24^3x48 gauss, mixed batch ({st.iters} iterations, {st.refine} in low precision)")
     del op, out, Wlo
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("prec,L,tol", [(bri.F64, (16, 16, 16, 14), 1e-13), (bri.F64, (20, 12, 14, 16), 1e-13),
+                                        (bri.F32, (30, 12, 16, 17), 1e-5)])
+def test_adjoint_in_reverse_order(prec, L, tol):
+    """Links between 256 and 512 MiB, where the adjoint takes the tiles in reverse order, at sampled sites: the
+    corners of the lattice, of the first and the last tile, and random ones."""
+    need_gpu()
+    V = int(np.prod(L))
+    assert (256 << 20) < V * 360 * (16 if prec == bri.F64 else 8) <= (512 << 20)
+    U = synth.random_links(L, 0.6, 6540)
+    W = bri.build_links(L, bri.links_to_device(U), prec, tbc=1)
+    psi = synth.gaussian_source(L, 6541)
+    sites = [0, 1, L[0] - 1, 63, 64, V - 1, V - 64, V - 65]
+    sites += [int(v) for v in np.random.default_rng(6542).integers(0, V, 56)]
+    print(f"[idle] adjoint {L} prec {prec}", flush=True)
+    got = bri.spinor_to_host(bri.apply_dag(L, W, prec, -0.9, bri.spinor_to_device(psi, prec)))[0]
+    ref = oracle.dirac_adj_at(L, U, 1, -0.9, psi[0], sites)
+    assert np.abs(got[sites] - ref).max() <= tol * np.abs(ref).max()
